@@ -88,7 +88,7 @@ def draw(rng):
         if do == "open":
             batch = min(batch, 2)
         prompts = " ".join(str(int(round(2.0 ** rng.uniform(6, 13)))) for _ in range(batch))
-        vocab = 0 if rng.random() < 0.7 else 16 * rng.randint(64, 2000)
+        vocab = 0 if rng.random() < 0.7 else 32 * rng.randint(32, 1000)
         draft = "none" if do == "verify" else rng.choice(["chain", "chain", "block", "cond"])
         rowmajor = rng.random() < 0.15 and batch * (K + 1) <= 64
         c = _case("", do, shape, rng.randint(1, 4), K, prompts, vocab, draft, rng.randint(1, 2), rowmajor,

@@ -113,6 +113,7 @@ struct Ctx {
   bf16_t* u = nullptr;              // [Mpad][ffn] SwiGLU output (max of both models)
   bf16_t* xg = nullptr;             // [Mpad][hidden] bf16(x * gain of the next RMSNorm)
   float* ss = nullptr;              // [hidden/16][Mpad] per-16-column sums of x^2
+  float* rinv = nullptr;            // wide contexts: [Mpad] 1/rms of each row of x
   float2* rcs = nullptr;            // [Mpad][head_dim/2] (cos, sin) of each row's rotary pairs
   float* part = nullptr;            // GEMV k-split partial sums
   size_t part_elems = 0;
@@ -163,7 +164,7 @@ struct Ctx {
   bool gemm_rows = false;              // layered row-major passes run on the batched-row GEMM
   bool gemm_pk = false;                // ... which streams the tile-packed weight copy
   bool gemm_wide = false;              // ... on the wide-unit kernel (passes of more than 32 rows)
-  bf16_t* xgp = nullptr;               // wide contexts: step-major copy of xg [H/32][M][32] for that kernel
+  bf16_t* xgp = nullptr;               // wide contexts: operand-order copy of xg (device.h) for that kernel
   bool poisoned = false;
   std::string err;
 

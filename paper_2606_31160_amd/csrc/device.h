@@ -41,6 +41,15 @@ __device__ __forceinline__ f32x4 mfma16x16x32(u32x4 a, u32x4 b, f32x4 c) {
                                                  0, 0, 0);
 }
 
+// Operand-order activations, [K/32][mb][64][8] for mb row blocks of 16 rows:
+// the block of (32-column step, row block) is the 1 KB B operand of one
+// 16x16x32 MFMA, lane l's 16 bytes (row l & 15, columns 8 (l >> 4) .. +8) at
+// 16 l, and consecutive blocks are one contiguous run, which buffer-to-LDS
+// loads copy as it is.  Element index of row m, column n.
+__device__ __forceinline__ size_t xop_at(int m, int n, int mb) {
+  return ((((size_t)(n >> 5) * mb + (m >> 4)) * 4 + ((n >> 3) & 3)) * 16 + (m & 15)) * 8 + (n & 7);
+}
+
 // Device-coherent accesses for data handed between workgroups of one launch
 // (possibly on different XCDs): relaxed agent-scope atomic loads and stores,
 // which go to the device's coherence point instead of the XCD's L2.  A writer

@@ -411,343 +411,391 @@ __global__ __launch_bounds__(threads_for(MB)) void k_gemm(GemvArgs a) {
 // ---------------------------------------------------------------------------
 // Wide-unit GEMM over the tile-packed weights for passes of 33 to 160 rows
 // (3 to 10 row blocks): the gate/up and LM-head projections in one launch, and
-// the q/k/v, o and down projections as k-split partial sums.  Gate/up and the
-// LM head run one workgroup per CU, each over an even, contiguous share of the
-// tile pairs walked in chunks of at most kWideTiles = 16 tiles (256 columns);
-// a k-split launch gives each workgroup 16 tiles and the k-range of split
-// blockIdx.y.  The 8 waves are 4 column groups x 2 k-groups: wave (cg, kg)
-// multiplies tiles 4 cg .. 4 cg + 3 over the kg-th half of the k-range, so
-// each x operand it reads from LDS feeds 4 MFMAs and each weight block MB of
-// them, and the two k-groups keep two independent streams of loads in flight.
-// Per 32-wide k-step each k-group stages the x operands of all rows by
-// buffer-to-LDS loads straight in MFMA operand order (block rb of a step: 16
-// rows x 32 columns, lane l's 16 bytes at 16 l) into its own ring of D + 1
-// slots, D steps ahead; weights go to registers the same depth ahead.  x is
-// read from a step-major copy where the producer wrote one (each block then
-// one contiguous 1 KB run), else from row-major rows.  One
-// barrier per step; its wait count is set by hand (every wave issues the same
-// loads per step: its share of its k-group's x blocks, then its 4 weight
-// blocks), so that every step in flight stays in flight.  A load past its
-// k-group's range or past the last tile gets an offset past the operand and
-// returns zeros without a memory access; rows past M read past the end of x
-// and are never stored.  At the end the second k-group's partial tiles are
-// added to the first's through LDS (first half + second half of the k-range),
-// and the first k-group runs the epilogue.
+// the q/k/v, o and down projections as k-split partial sums.
+//
+// A unit is a pair of tiles (32 output columns; a gate/up pair).  A workgroup
+// takes a contiguous run of units over the k-range of its split, walked in
+// chunks of at most P units.  Wave 0 only stages x; P x KG worker waves
+// multiply: worker (p, kg) owns unit p of the chunk and, of every stage of
+// KG x NS k-steps, the kg-th NS steps, for all row blocks, so that each x
+// operand read from LDS feeds two MFMAs and each weight block MB of them.
+//
+// x: the loader wave stages a stage's x operands (all rows) by buffer-to-LDS
+// loads, in MFMA operand order (block rb of a step: 16 rows x 32 columns, lane
+// l's 16 bytes at 16 l), into one of two LDS buffers while the workers use the
+// other; one workgroup barrier per stage.  Weights go straight to the workers'
+// registers, kWideDepth steps ahead.  With x in a wave of its own, a worker's
+// only outstanding memory operations are its weight loads, so the compiler's
+// wait counts are exact and the loads stay in flight across the barriers.
+//
+// What bounds it: the weights, read once from HBM, then the work at both ends
+// of a launch.  x comes from the XCD's L2 (a workgroup reads up to 112 GB/s per
+// CU of lines its neighbours share, against 27 GB/s per CU of HBM at full
+// rate), so narrow column ranges with few k-splits beat wide ones with many:
+// re-reading x is cheaper than writing and re-reading fp32 partial sums.  One
+// barrier per stage instead of per k-step, x in waves of its own, and no 64-bit
+// division, dependent load or unrolled epilogue around the loop: at 144 rows
+// and 7B widths gate/up 87 -> 56 us, LM head 315 -> 207, down 40 -> 33, q/k/v
+// 21 -> 17, o 22 -> 14.5; at 45 rows 51 -> 45, 201 -> 182, 27 (unchanged), 15 ->
+// 11.6 and 15 -> 9.4.  Of the 56 us, 42 are the loop (39 us of weights at the
+// read rate), 4 the time to the first staged x and 5 the epilogue.
+//
+// A weight load past the k-range or the unit range gets an offset past the
+// operand and returns zeros without a memory access; steps past the k-range
+// are not multiplied; rows past M read other rows' x and are never stored.
 // ---------------------------------------------------------------------------
-constexpr int kWideTiles = 16;
-constexpr int kWideWaves = 8;
-constexpr int kWideCg = 4;                          // column groups
-constexpr int kWideTpw = kWideTiles / kWideCg;      // tiles per wave
-constexpr int kWideSlice = 8;                       // sums of squares per partial of the 1/rms prologue
-// steps in flight per k-group: 4, or 3 for 9 and 10 row blocks (whose
-// accumulators take 144 and 160 of a wave's 256 registers)
-constexpr int wide_depth(int mb) { return mb >= 9 ? 3 : 4; }
+constexpr int kWideLoaders = 2;     // waves that stage x
+// worker waves: 14, or 10 from 7 row blocks, whose accumulators (8 registers
+// per row block) leave no room for the weights in a 16-wave workgroup's 128
+constexpr int wide_workers(int mb) { return mb <= 6 ? 14 : 10; }
+constexpr int kWideDepth = 4;       // weight k-steps in flight per worker
 
+// Buffer-to-LDS load of 16 bytes per lane; IMM is added to both addresses.
+template <int IMM>
 __device__ __forceinline__ void lds_load16(__amdgpu_buffer_rsrc_t r, unsigned char* dst, int voff) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(dst), 16, voff, 0, 0, 0);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(dst), 16, voff, 0, IMM, 0);
 }
 
-// the two x rings, the dummy block (target of the spare x loads) and the
-// 1/rms partials; the final k-group sum reuses the rings (8 MB blocks)
-size_t wide_lds_bytes(int mb, int H) {
-  const int nsl = (H / kTile + kWideSlice - 1) / kWideSlice;
-  return (size_t)2 * (wide_depth(mb) + 1) * mb * 1024 + 1024 + (size_t)nsl * 16 * mb * sizeof(float);
+// Workgroup barrier that waits for this wave's LDS operations only.
+__device__ __forceinline__ void wide_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// k-steps per worker and stage for KG k-groups of MB row blocks, and the stage
+// buffers
+constexpr size_t kWideRing = 144 * 1024;
+constexpr int kWideStages = 6;
+int wide_ns(int mb, int kg) {
+  for (int ns : {4, 2})
+    if ((size_t)2 * kg * ns * mb * 1024 <= kWideRing) return ns;
+  return 1;
+}
+int wide_nb(int mb, int kg) {
+  return (int)std::min<size_t>(kWideStages, kWideRing / ((size_t)kg * wide_ns(mb, kg) * mb * 1024));
 }
 
-template <int MB, int EPI>
-__global__ __launch_bounds__(kWideWaves * 64, 1) void k_gemm_wide(GemvArgs a) {
+// Row blocks whose partial tiles (P units, KG k-groups) pass through LDS at once.
+int wide_rb(int mb, int P, int KG) { return std::max(1, std::min(mb, (int)(kWideRing / ((size_t)KG * P * 2 * 1024)))); }
+// The x stage buffers, reused by the partial tiles; the LM head's running
+// (max, index) of every unit slot and row.
+size_t wide_lds_bytes(int mb, int P, int KG, int epi) {
+  const size_t ring = (size_t)wide_nb(mb, KG) * KG * wide_ns(mb, KG) * mb * 1024;
+  const size_t sums = (size_t)wide_rb(mb, P, KG) * KG * P * 2 * 1024;
+  return std::max(ring, sums) + (epi == EPI_ARGMAX ? (size_t)P * 16 * mb * 8 : 0);
+}
+
+// Waits until at most n of the wave's vector memory operations are in flight
+// (n rounded down to a multiple of four).
+__device__ __forceinline__ void wait_vm(int n) {
+  switch (min(n, 60) >> 2) {
+#define WVM(i) case i: asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * i) : "memory"); break;
+    WVM(1) WVM(2) WVM(3) WVM(4) WVM(5) WVM(6) WVM(7) WVM(8) WVM(9) WVM(10) WVM(11) WVM(12) WVM(13) WVM(14) WVM(15)
+#undef WVM
+    default: asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  }
+}
+
+template <int MB, int EPI, int NS>
+__global__ __launch_bounds__((wide_workers(MB) + kWideLoaders) * 64) void k_gemm_wide(GemvArgs a) {
   static_assert(EPI == EPI_SWIGLU || EPI == EPI_ARGMAX || EPI == EPI_STORE, "wide-unit epilogues");
   constexpr bool kNorm = EPI != EPI_STORE;
-  constexpr int ROWS = 16 * MB, TPW = kWideTpw, D = wide_depth(MB), NB = D + 1, NT = kWideWaves * 64;
-  constexpr int XPW = (MB + kWideCg - 1) / kWideCg;   // x blocks each wave stages per step
-  // loads issued after step c's x loads while they are awaited: that step's
-  // weights, then D - 1 steps of both
-  constexpr int WAITN = TPW + (D - 1) * (XPW + TPW);
-  static_assert(2 * NB >= 2 * kWideCg, "the k-group sum reuses the x rings");
-  static_assert(TPW == 4, "the weight wait names four register tuples");
+  constexpr int ROWS = 16 * MB, D = kWideDepth, U = D / NS;   // U stages per unrolled round
   extern __shared__ __align__(16) unsigned char lds[];
-  __shared__ float inv_rms[ROWS];
+  __shared__ float inv_rms[ROWS];       // 0 for rows past the pass or idle
   __shared__ int live_s[ROWS];
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
-  const int cg = wave % kWideCg, kg = wave / kWideCg;
-  const int M = a.M, N = a.N, ntiles = N / kTile;
-  const int T = (a.Kd + 31) >> 5;
-  const int split = blockIdx.y;
-  const int s0 = (int)((long long)split * T / a.splits), s1 = (int)((long long)(split + 1) * T / a.splits);
-  const int half = (s1 - s0 + 1) >> 1;
-  const int kb = kg ? s0 + half : s0, ke = kg ? s1 : s0 + half;   // this k-group's steps [kb, ke)
-  // Units of two tiles (a gate/up pair).  SwiGLU and argmax: contiguous
-  // ranges of units dealt evenly to the gridDim.x workgroups (one per CU), so
-  // that every CU streams the same share of the weights, each range walked in
-  // chunks of at most 8 units (16 tiles); k-split partial sums: 8 units per
-  // workgroup.
-  const int nunits = ntiles >> 1;
-  int u0, u1;
-  if constexpr (EPI == EPI_STORE) {
-    u0 = blockIdx.x * (kWideTiles / 2);
-    u1 = min(u0 + kWideTiles / 2, nunits);
+  const int M = a.M, N = a.N, T = (a.Kd + 31) >> 5, ntiles = N / kTile, nunits = (ntiles + 1) >> 1;
+  // The divisions are the host's: the code ahead of the first loads is fetched
+  // cold by every launch.
+  const int P = a.wp, KG = a.wkg, NB = a.wnb, nch = a.wnch, cu = a.wcu, nst = a.wnst;
+  // Splits are dealt first: consecutive workgroups go to the 8 XCDs in turn, so
+  // with 2, 4 or 8 splits an XCD's workgroups share one split's x in its L2.
+  const int split = blockIdx.x % a.splits, blk = blockIdx.x / a.splits;
+  const int s0 = split * a.wsq + min(split, a.wsr), s1 = s0 + a.wsq + (split < a.wsr ? 1 : 0);
+  const int u0 = blk * a.wuq + min(blk, a.wur), u1 = u0 + a.wuq + (blk < a.wur ? 1 : 0);
+  const int SS = KG * NS;                                     // k-steps per stage
+  const int stage_bytes = SS * MB * 1024;
+  float* best_v = reinterpret_cast<float*>(lds + a.wlds - (size_t)P * ROWS * 8);   // LM head: [P][ROWS] running
+  int* best_i = reinterpret_cast<int*>(best_v + P * ROWS);                          // maximum and its index
+
+  if (wave < kWideLoaders) {
+    // The loaders share every stage's x blocks.  Operand-order x: a stage is
+    // one contiguous run, four 1 KB blocks per address.  Row-major x: lane l
+    // reads row 16 b + (l & 15), 16 bytes at column 32 step + 8 (l >> 4).
+    // (Steps past the range are never multiplied.)
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(a.x), 0,
+                                                                        a.xpk ? T * MB * 1024 : M * a.ldx * 2, kRsrcWord3);
+    const int nblk = SS * MB, b0 = nblk * wave / kWideLoaders, b1 = nblk * (wave + 1) / kWideLoaders, cnt = b1 - b0;
+    auto issue = [&](int st, int slot) {
+      unsigned char* dst = lds + slot * stage_bytes;
+      const int step0 = s0 + st * SS;
+      if (a.xpk) {
+        int off = (step0 * MB + b0) * 1024 + 16 * lane;
+        int k = b0;
+        for (; k + 4 <= b1; k += 4, off += 4096) {
+          lds_load16<0>(rx, dst + k * 1024, off);
+          lds_load16<1024>(rx, dst + k * 1024, off);
+          lds_load16<2048>(rx, dst + k * 1024, off);
+          lds_load16<3072>(rx, dst + k * 1024, off);
+        }
+        for (; k < b1; ++k, off += 1024) lds_load16<0>(rx, dst + k * 1024, off);
+      } else {
+        const int xlane = ((lane & 15) * a.ldx + 8 * (lane >> 4)) * 2;
+        for (int k = b0; k < b1; ++k)
+          lds_load16<0>(rx, dst + k * 1024, xlane + (step0 + k / MB) * 64 + (k % MB) * 32 * a.ldx);
+      }
+    };
+    // what the epilogues need: loaded first (one round trip, beside the x
+    // loads), stored to LDS below
+    constexpr int RPT = (ROWS + kWideLoaders * 64 - 1) / (kWideLoaders * 64);   // rows per loader thread
+    int cnt_r[RPT] = {}, row_j[RPT] = {};
+    float inv_r[RPT] = {};
+    if constexpr (kNorm) {
+#pragma unroll
+      for (int i = 0; i < RPT; ++i) {
+        const int m = min((int)threadIdx.x + i * kWideLoaders * 64, M - 1), b = m / a.rps;
+        row_j[i] = m - b * a.rps;
+        cnt_r[i] = a.st[b].count;
+        inv_r[i] = a.rinv[m];
+      }
+    }
+    for (int ch = 0; ch < nch; ++ch) {
+      const int ahead = min(NB - 1, nst);
+      for (int st = 0; st < ahead; ++st) issue(st, st);
+      if (ch == 0) {
+        if constexpr (kNorm) {
+#pragma unroll
+          for (int i = 0; i < RPT; ++i) {
+            const int m = threadIdx.x + i * kWideLoaders * 64;
+            const bool lv = m < M && row_j[i] < cnt_r[i];
+            if (m < ROWS) {
+              live_s[m] = lv ? 1 : 0;
+              inv_rms[m] = lv ? inv_r[i] : 0.f;
+            }
+          }
+        }
+        if constexpr (EPI == EPI_ARGMAX) {
+          for (int i = threadIdx.x; i < P * ROWS; i += kWideLoaders * 64) {
+            best_v[i] = -INFINITY;
+            best_i[i] = 0x7fffffff;
+          }
+        }
+      }
+      int slot = ahead == NB ? 0 : ahead;     // the next stage's buffer
+      if (slot >= NB) slot -= NB;
+      for (int st = 0; st < nst; ++st) {
+        wait_vm(min(NB - 2, nst - 1 - st) * cnt);
+        wide_barrier();                       // stage st is staged; the buffer of stage st - 1 is free
+        if (st + NB - 1 < nst) {
+          issue(st + NB - 1, slot);
+          if (++slot == NB) slot = 0;
+        }
+      }
+      wide_barrier();                         // the workers are done with the last stage
+      if (EPI == EPI_STORE && KG == 1) continue;
+      for (int r0 = 0; r0 < MB; r0 += a.wrb) {
+        wide_barrier();
+        wide_barrier();
+      }
+    }
   } else {
-    u0 = (int)((long long)blockIdx.x * nunits / gridDim.x);
-    u1 = (int)((long long)(blockIdx.x + 1) * nunits / gridDim.x);
-  }
-  const int nch = (u1 - u0 + kWideTiles / 2 - 1) / (kWideTiles / 2);
-  const int cu = nch > 0 ? (u1 - u0 + nch - 1) / nch : 1;   // units per chunk
-  int tile0 = 0, tend = 0;   // this wave's first tile, the chunk's end tile
-  // step-major x spans whole 32-wide steps (its buffer is padded to them:
-  // columns past Kd meet zero weight columns)
-  const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(a.x), 0,
-                                                                      a.xpk ? T * M * 64 : M * a.ldx * 2, kRsrcWord3);
-  unsigned char* ring = lds + (size_t)kg * NB * MB * 1024;           // [NB][MB] blocks of 1 KB
-  unsigned char* dummy = lds + (size_t)2 * NB * MB * 1024;           // target of the spare x loads
-  float* rms_part = reinterpret_cast<float*>(dummy + 1024);          // [slices][ROWS]
-  const int nt16 = kNorm ? a.H / kTile : 0, nsl = (nt16 + kWideSlice - 1) / kWideSlice;
+    const int wi = wave - kWideLoaders, kg = (wi * a.wrp) >> 16, pi = wi - kg * P;
+    // Weights of the chunk being refilled: one buffer per tile, ending at the
+    // split's last step, so that later steps (and, with no bytes at all, a slot
+    // without a unit) read zeros without a memory access or a branch.
+    __amdgpu_buffer_rsrc_t rw[2];
+    auto open_w = [&](int ch) {
+      const int unit = u0 + ch * cu + pi;
+      const bool on = ch < nch && pi < cu && unit < u1;
+      const bf16_t* p = a.pw + (size_t)(on ? 2 * unit : 0) * T * 512;
+      rw[0] = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p), 0, on ? s1 * 1024 : 0, kRsrcWord3);
+      rw[1] = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p + (size_t)T * 512), 0,
+                                                on && 2 * unit + 1 < ntiles ? s1 * 1024 : 0, kRsrcWord3);
+    };
+    const int w0 = (s0 + kg * NS) * 1024 + 16 * lane;         // the worker's first step of stage 0
+    u32x4 w[D][2];
+    auto issue_w = [&](u32x4 (&wr)[2], int off) {
+      wr[0] = __builtin_amdgcn_raw_buffer_load_b128(rw[0], off, 0, kNt);
+      wr[1] = __builtin_amdgcn_raw_buffer_load_b128(rw[1], off, 0, kNt);
+    };
+    open_w(0);
+#pragma unroll
+    for (int uu = 0; uu < U; ++uu)
+#pragma unroll
+      for (int i = 0; i < NS; ++i) {
+        issue_w(w[uu * NS + i], w0 + (uu * SS + i) * 1024);
+        asm volatile("" ::: "memory");   // in this order: the wait counts of the loop's first round follow it
+      }
 
-  for (int m = threadIdx.x; m < ROWS; m += NT) {
-    int lv = 0;
-    if (m < M) {
-      const int b = m / a.rps;
-      lv = (m - b * a.rps) < a.st[b].count ? 1 : 0;
-    }
-    live_s[m] = lv;
-  }
-
-  // x operand of block b at step st: byte offset xbase[j] + st * xstride;
-  // lane l reads row 16 b + (l & 15), 16 bytes at column 32 st + 8 (l >> 4)
-  // (MFMA operand order).  Row-major x: 16 rows of 64 bytes ldx apart.
-  // Step-major x (xpk, [Kd/32][M][32]): the block is one contiguous 1 KB run.
-  const int xstride = a.xpk ? M * 64 : 64;
-  int xbase[XPW];
+    for (int ch = 0; ch < nch; ++ch) {
+      f32x4 acc[2][MB];
 #pragma unroll
-  for (int j = 0; j < XPW; ++j) {
-    const int b = cg + kWideCg * j;
-    const int r = 16 * b + (lane & 15);
-    xbase[j] = a.xpk ? r * 64 + 16 * (lane >> 4) : (r * a.ldx + 8 * (lane >> 4)) * 2;
-  }
-  const int lane_w = 16 * lane;
-  // Offsets past a k-group's range or the last tile are ORed with kOut (a
-  // wave-uniform scalar select): every offset stays below 2^31, so the result
-  // lies past the operand, and no branch splits the loads (a branch would
-  // make the compiler drain every load in flight where the paths join).
-  auto issue_x = [&](int c) {
-    const int st = kb + c;
-    const int oob = st < ke ? 0 : kOut;
-    unsigned char* slot = ring + (c % NB) * (MB * 1024);
+      for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int j = 0; j < XPW; ++j) {
-      const int b = cg + kWideCg * j;
-      const int ob = b < MB ? oob : kOut;
-      lds_load16(rx, b < MB ? slot + b * 1024 : dummy, (xbase[j] + st * xstride) | ob);
-    }
-  };
-  // The weight loads are written as inline assembly, and waited for by hand
-  // below.  The compiler's own wait counts leave out the buffer-to-LDS loads
-  // it issues between them, so they would wait for several steps' loads at
-  // once where one step's are due.
-  const uint64_t wbase = reinterpret_cast<uint64_t>(a.pw);
-  const u32x4 wdesc = u32x4{(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)wbase),
-                            (uint32_t)__builtin_amdgcn_readfirstlane((int)((wbase >> 32) & 0xffffu)),
-                            (uint32_t)(ntiles * T * 1024), (uint32_t)kRsrcWord3};
-  auto issue_w = [&](int c, u32x4 (&wr)[TPW]) {
-    const int st = kb + c;
-    const int oob = st < ke ? 0 : kOut;
-#pragma unroll
-    for (int t = 0; t < TPW; ++t) {
-      const int ot = tile0 + t < tend ? oob : kOut;
-      const int off = (lane_w + ((tile0 + t) * T + st) * 1024) | ot;
-      asm volatile("buffer_load_dwordx4 %0, %1, %2, 0 offen nt" : "=v"(wr[t]) : "v"(off), "s"(wdesc) : "memory");
-    }
-  };
-
-  // 1/rms, first half: partial sums of kWideSlice consecutive per-16-column
-  // sums of squares per (slice, row)
-  if constexpr (kNorm) {
-    for (int it = threadIdx.x; it < nsl * ROWS; it += 4 * NT) {   // up to 4 items per thread and round
-      float v[4][kWideSlice];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int item = it + r * NT, sl = item / ROWS, m = item % ROWS;
-#pragma unroll
-        for (int k = 0; k < kWideSlice; ++k) {
-          const int g = sl * kWideSlice + k;
-          v[r][k] = (item < nsl * ROWS && g < nt16) ? a.ss_in[(size_t)g * a.mpad + m] : 0.f;
+        for (int mb = 0; mb < MB; ++mb) acc[t][mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+      int slot = 0;                                           // the stage's buffer
+      for (int st0 = 0; st0 < nst; st0 += U) {
+        int wn = w0 + (st0 + U) * SS * 1024;                  // the refills' steps
+        if (st0 + U >= nst) {                                 // ... which belong to the next chunk
+          open_w(ch + 1);
+          wn = w0;
         }
-      }
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int item = it + r * NT;
-        float sum = 0.f;
+        for (int uu = 0; uu < U; ++uu) {
+          wide_barrier();
+          const unsigned char* xb = lds + slot * stage_bytes + kg * NS * MB * 1024 + 16 * lane;
+          if (++slot == NB) slot = 0;
 #pragma unroll
-        for (int k = 0; k < kWideSlice; ++k) sum += v[r][k];
-        if (item < nsl * ROWS) rms_part[item] = sum;
-      }
-    }
-    __syncthreads();
-    // 1/rms, second half: the slices of each row in order
-    for (int m = threadIdx.x; m < ROWS; m += NT) {
-      float t = 0.f;
-      for (int sl = 0; sl < nsl; ++sl) t += rms_part[sl * ROWS + m];
-      inv_rms[m] = live_s[m] ? rsqrtf(t / a.H + a.eps) : 0.f;
-    }
-  }
-  __syncthreads();
-
-  for (int cs = u0; cs < u1; cs += cu) {   // workgroup-uniform
-  tile0 = 2 * cs + cg * TPW;
-  tend = 2 * min(cs + cu, u1);
-  u32x4 wr[D][TPW];
+          for (int i = 0; i < NS; ++i) {
+            u32x4(&ws)[2] = w[uu * NS + i];
+            if (s0 + (st0 + uu) * SS + kg * NS + i < s1) {    // wave-uniform
+              u32x4 xv[MB];
 #pragma unroll
-  for (int i = 0; i < D; ++i) {
-    issue_x(i);
-    issue_w(i, wr[i]);
-  }
-  f32x4 acc[TPW][MB];
+              for (int mb = 0; mb < MB; ++mb) xv[mb] = *reinterpret_cast<const u32x4*>(xb + (i * MB + mb) * 1024);
 #pragma unroll
-  for (int t = 0; t < TPW; ++t)
+              for (int mb = 0; mb < MB; ++mb) {
+                acc[0][mb] = mfma16x16x32(ws[0], xv[mb], acc[0][mb]);
+                acc[1][mb] = mfma16x16x32(ws[1], xv[mb], acc[1][mb]);
+              }
+              // kXv operand reads ahead of the products that use them
+              constexpr int kXv = MB < 4 ? MB : MB == 6 ? 3 : 4;
+              __builtin_amdgcn_sched_group_barrier(0x100, kXv, 0);
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) acc[t][mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int c0 = 0; c0 < half; c0 += D) {   // workgroup-uniform
-#pragma unroll
-    for (int uu = 0; uu < D; ++uu) {
-      const int c = c0 + uu;
-      // step c's x (every wave's share) has landed and is visible; the
-      // memory clobbers keep LDS accesses on their side of the barrier
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(WAITN) : "memory");
-      __builtin_amdgcn_s_barrier();
-      asm volatile("" ::: "memory");
-      const unsigned char* xb = ring + (c % NB) * (MB * 1024) + 16 * lane;
-      // step c's weights: the loads issued after them are D - 1 steps of x
-      // and weights; the registers are operands of the wait, so nothing reads
-      // them before it
-      asm volatile("s_waitcnt vmcnt(%4)"
-                   : "+v"(wr[uu][0]), "+v"(wr[uu][1]), "+v"(wr[uu][2]), "+v"(wr[uu][3])
-                   : "n"((D - 1) * (XPW + TPW))
-                   : "memory");
-      u32x4 w[TPW];
-#pragma unroll
-      for (int t = 0; t < TPW; ++t) w[t] = wr[uu][t];
-      if (kb + c < ke) {   // wave-uniform
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-          const u32x4 xv = *reinterpret_cast<const u32x4*>(xb + mb * 1024);
-#pragma unroll
-          for (int t = 0; t < TPW; ++t) acc[t][mb] = mfma16x16x32(w[t], xv, acc[t][mb]);
-        }
-      }
-      asm volatile("" ::: "memory");
-      // slot (c + D) % NB was last read at step c - 1, before this step's barrier
-      issue_x(c + D);
-      issue_w(c + D, wr[uu]);
-    }
-  }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the spare loads past the end
-  __syncthreads();
-
-  // the second k-group's partial tiles onto the first's, two tiles at a time
-  f32x4* red = reinterpret_cast<f32x4*>(lds);   // [2][kWideCg][MB][64]
-#pragma unroll
-  for (int h = 0; h < TPW / 2; ++h) {
-    if (kg == 1) {
-#pragma unroll
-      for (int tt = 0; tt < 2; ++tt)
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) red[((tt * kWideCg + cg) * MB + mb) * 64 + lane] = acc[2 * h + tt][mb];
-    }
-    __syncthreads();
-    if (kg == 0) {
-#pragma unroll
-      for (int tt = 0; tt < 2; ++tt)
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) acc[2 * h + tt][mb] += red[((tt * kWideCg + cg) * MB + mb) * 64 + lane];
-    }
-    __syncthreads();
-  }
-  if (kg == 0) {
-  const int grp = lane >> 4;
-  if constexpr (EPI == EPI_STORE) {
-    // fp32 partial sums of this split: out[split][m][n]
-#pragma unroll
-    for (int t = 0; t < TPW; ++t) {
-      const int tile = tile0 + t;
-      if (tile >= tend) continue;
-      const int n = tile * kTile + 4 * grp;
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) {
-        const int m = mb * 16 + (lane & 15);
-        if (m < M) *reinterpret_cast<f32x4*>(a.out + ((size_t)split * M + m) * N + n) = acc[t][mb];
-      }
-    }
-  } else if constexpr (EPI == EPI_SWIGLU) {
-    // tiles tile0 + 2j, tile0 + 2j + 1: the gate and up rows of features
-    // 16 (tile0 / 2 + j) .. +16
-    const int F = N / 2;
-#pragma unroll
-    for (int j = 0; j < TPW / 2; ++j) {
-      const int f = ((tile0 >> 1) + j) * kTile + 4 * grp;
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) {
-        const int m = mb * 16 + (lane & 15);
-        if (m >= M || f >= F || tile0 + 2 * j >= tend) continue;
-        const float r = inv_rms[m];
-        float o[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float g = acc[2 * j][mb][i] * r, up = acc[2 * j + 1][mb][i] * r;
-          o[i] = live_s[m] ? g / (1.f + expf(-g)) * up : 0.f;
-        }
-        const size_t at = a.upk ? ((size_t)(f >> 5) * M + m) * 32 + (f & 31) : (size_t)m * F + f;
-        *reinterpret_cast<u32x2*>(a.u + at) = u32x2{pack2(o[0], o[1]), pack2(o[2], o[3])};
-      }
-    }
-  } else {   // EPI_ARGMAX: per tile and row, the (max, index) of its 16 logits
-#pragma unroll
-    for (int t = 0; t < TPW; ++t) {
-      const int tile = tile0 + t;
-      if (tile >= tend) continue;
-      const int n = tile * kTile + 4 * grp;
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) {
-        const int m = mb * 16 + (lane & 15);
-        const int mm = m < ROWS ? m : ROWS - 1;
-        const bool live = m < M && live_s[mm];
-        const float r = inv_rms[mm];
-        float y[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) y[i] = live ? acc[t][mb][i] * r : 0.f;
-        if (a.allow_logits && m < M && a.st[m / a.rps].want_logits)
-          *reinterpret_cast<u32x2*>(a.logits + (size_t)m * N + n) = u32x2{pack2(y[0], y[1]), pack2(y[2], y[3])};
-        float best = -INFINITY;
-        int bi = n;
-        int nan = 0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          float v = y[i];
-          if (v != v) {
-            nan = 1;
-            v = -INFINITY;
-          }
-          if (v > best) {
-            best = v;
-            bi = n + i;
+              for (int mb = 0; mb < MB - kXv; ++mb) {
+                __builtin_amdgcn_sched_group_barrier(0x8, 2, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+              }
+              __builtin_amdgcn_sched_group_barrier(0x8, 2 * kXv, 0);
+            }
+            issue_w(ws, wn + (uu * SS + i) * 1024);
           }
         }
+      }
+      wide_barrier();
+      const int unit = u0 + ch * cu + pi, grp = lane >> 4;
+      const bool mine = pi < cu && unit < u1;                 // wave-uniform
+      const bool two = 2 * unit + 1 < ntiles;                 // the last unit may be a single tile
+      if constexpr (EPI == EPI_STORE) {
+        if (KG == 1) {   // complete sums of this split: out[split][m][n]
+          float* o = a.out + ((size_t)split * M + (lane & 15)) * N + 2 * unit * kTile + 4 * grp;
 #pragma unroll
-        for (int o = 16; o <= 32; o <<= 1) {
-          const float v2 = __shfl_xor(best, o);
-          const int i2 = __shfl_xor(bi, o);
-          nan |= __shfl_xor(nan, o);
-          amax_merge(best, bi, v2, i2);
+          for (int mb = 0; mb < MB; ++mb, o += (size_t)16 * N)
+            if (mine && mb * 16 + (lane & 15) < M) {
+              *reinterpret_cast<f32x4*>(o) = acc[0][mb];
+              if (two) *reinterpret_cast<f32x4*>(o + kTile) = acc[1][mb];
+            }
+          continue;
         }
-        if (grp == 0 && m < M) {
-          a.amax_v[(size_t)tile * a.mpad + m] = best;
-          a.amax_i[(size_t)tile * a.mpad + m] = bi;
-          if (nan && live) atomicOr(const_cast<int32_t*>(&a.st[m / a.rps].err), ERR_NUMERIC);
+      }
+      // The partial tiles go through LDS, a.wrb row blocks at a time; worker
+      // (p, kg) then completes unit p's row blocks kg, kg + KG, .., adding the
+      // k-groups' partial tiles in order.  That loop is kept rolled: unrolled
+      // over the row blocks it would be several KB of code that every launch
+      // fetches once.
+      f32x4* red = reinterpret_cast<f32x4*>(lds) + lane;      // [KG][P][2][wrb][64]
+      for (int r0 = 0; r0 < MB; r0 += a.wrb) {
+        const int nr = min(a.wrb, MB - r0);
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+          if (mb >= r0 && mb < r0 + nr) {                     // wave-uniform
+            f32x4* r = red + ((kg * P + pi) * 2 * a.wrb + mb - r0) * 64;
+            r[0] = acc[0][mb];
+            r[a.wrb * 64] = acc[1][mb];
+          }
+        wide_barrier();
+#pragma unroll 1
+        for (int rb = mine ? kg : nr; rb < nr; rb += KG) {
+          f32x4 y0 = f32x4{0.f, 0.f, 0.f, 0.f}, y1 = y0;
+#pragma unroll 1
+          for (int k = 0; k < KG; ++k) {
+            const f32x4* r = red + ((k * P + pi) * 2 * a.wrb + rb) * 64;
+            y0 += r[0];
+            y1 += r[a.wrb * 64];
+          }
+          const int m = (r0 + rb) * 16 + (lane & 15);
+          if constexpr (EPI == EPI_STORE) {
+            // fp32 partial sums of this split: out[split][m][n]
+            if (m < M) {
+              float* o = a.out + ((size_t)split * M + m) * N + 2 * unit * kTile + 4 * grp;
+              *reinterpret_cast<f32x4*>(o) = y0;
+              if (two) *reinterpret_cast<f32x4*>(o + kTile) = y1;
+            }
+          } else if constexpr (EPI == EPI_SWIGLU) {
+            // the gate and up rows of features 16 unit .. +16
+            const int F = N / 2, f = unit * kTile + 4 * grp;
+            const float r = inv_rms[m];
+            const bool lv = live_s[m];
+            float o[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const float g = y0[i] * r, up = y1[i] * r;
+              o[i] = lv ? g / (1.f + expf(-g)) * up : 0.f;
+            }
+            if (m < M) {
+              const size_t at = a.upk ? xop_at(m, f, MB) : (size_t)m * F + f;
+              *reinterpret_cast<u32x2*>(a.u + at) = u32x2{pack2(o[0], o[1]), pack2(o[2], o[3])};
+            }
+          } else {   // EPI_ARGMAX: the (max, index) of each row over the unit's 32 logits
+            const int n = 2 * unit * kTile + 4 * grp;
+            const bool lv = live_s[m];
+            const float r = inv_rms[m];
+            float y[8];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              y[i] = lv ? y0[i] * r : 0.f;
+              y[4 + i] = lv ? y1[i] * r : 0.f;
+            }
+            if (a.allow_logits && m < M && a.st[m / a.rps].want_logits) {
+              bf16_t* lo = a.logits + (size_t)m * N + n;
+              *reinterpret_cast<u32x2*>(lo) = u32x2{pack2(y[0], y[1]), pack2(y[2], y[3])};
+              if (two) *reinterpret_cast<u32x2*>(lo + kTile) = u32x2{pack2(y[4], y[5]), pack2(y[6], y[7])};
+            }
+            float best = -INFINITY;
+            int bi = n;
+            int nan = 0;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+              float v = y[i];
+              if (i >= 4 && !two) v = -INFINITY;
+              if (v != v) {
+                nan = 1;
+                v = -INFINITY;
+              }
+              if (v > best) {
+                best = v;
+                bi = n + (i & 3) + (i >> 2) * kTile;
+              }
+            }
+#pragma unroll
+            for (int o = 16; o <= 32; o <<= 1) {
+              const float v2 = __shfl_xor(best, o);
+              const int i2 = __shfl_xor(bi, o);
+              nan |= __shfl_xor(nan, o);
+              amax_merge(best, bi, v2, i2);
+            }
+            if (grp == 0) {
+              float bv = best_v[pi * ROWS + m];
+              int bx = best_i[pi * ROWS + m];
+              amax_merge(bv, bx, best, bi);
+              best_v[pi * ROWS + m] = bv;
+              best_i[pi * ROWS + m] = bx;
+              if (nan && lv) atomicOr(const_cast<int32_t*>(&a.st[m / a.rps].err), ERR_NUMERIC);
+            }
+          }
         }
+        wide_barrier();
       }
     }
   }
-  }   // kg == 0
-  __syncthreads();   // the chunk's LDS reads are done before the next chunk's loads land
-  }   // chunks
+  if constexpr (EPI == EPI_ARGMAX) {
+    // one (max, index) per row for the whole workgroup
+    wide_barrier();
+    for (int m = threadIdx.x; m < M; m += blockDim.x) {
+      float bv = -INFINITY;
+      int bx = 0x7fffffff;
+      for (int p = 0; p < P; ++p) amax_merge(bv, bx, best_v[p * ROWS + m], best_i[p * ROWS + m]);
+      a.amax_v[(size_t)blk * a.mpad + m] = bv;
+      a.amax_i[(size_t)blk * a.mpad + m] = bx;
+    }
+  }
 }
 
 // CUs of the current device (the wide kernel's grid for SwiGLU and argmax)
@@ -761,33 +809,111 @@ int wide_cus() {
   return n;
 }
 
-template <int EPI>
-hipError_t launch_wide(const GemvArgs& g, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  const int mb = (g.M + 15) / 16;
-  const int groups = (g.N / kTile + kWideTiles - 1) / kWideTiles;
-  const dim3 grid(EPI == EPI_STORE ? groups : std::min(wide_cus(), g.N / kTile / 2), g.splits), block(kWideWaves * 64);
-  const size_t lds = wide_lds_bytes(mb, EPI == EPI_STORE ? 0 : g.H);
-  switch (mb) {
-    case 3: hipExtLaunchKernelGGL((k_gemm_wide<3, EPI>), grid, block, lds, s, e0, e1, 0, g); break;
-    case 4: hipExtLaunchKernelGGL((k_gemm_wide<4, EPI>), grid, block, lds, s, e0, e1, 0, g); break;
-    case 5: hipExtLaunchKernelGGL((k_gemm_wide<5, EPI>), grid, block, lds, s, e0, e1, 0, g); break;
-    case 6: hipExtLaunchKernelGGL((k_gemm_wide<6, EPI>), grid, block, lds, s, e0, e1, 0, g); break;
-    case 7: hipExtLaunchKernelGGL((k_gemm_wide<7, EPI>), grid, block, lds, s, e0, e1, 0, g); break;
-    case 8: hipExtLaunchKernelGGL((k_gemm_wide<8, EPI>), grid, block, lds, s, e0, e1, 0, g); break;
-    case 9: hipExtLaunchKernelGGL((k_gemm_wide<9, EPI>), grid, block, lds, s, e0, e1, 0, g); break;
-    case 10: hipExtLaunchKernelGGL((k_gemm_wide<10, EPI>), grid, block, lds, s, e0, e1, 0, g); break;
+// Geometry of a wide-unit launch: G workgroups per k-split, chunks of at most
+// P units, KG k-groups.  Workgroups divide the units evenly; P x KG workers
+// (at most wide_workers) share a workgroup's chunk.
+struct WidePlan {
+  int G, S, P, KG;
+};
+
+WidePlan wide_plan(int epi, int N, int Kd, int M, int ncu) {
+  const int mb = (M + 15) / 16, T = (Kd + 31) / 32, units = (N / kTile + 1) / 2;
+  auto shape = [&](int S) {
+    WidePlan p;
+    p.S = S;
+    p.G = std::max(1, std::min(ncu / S, units));
+    const int upw = (units + p.G - 1) / p.G;                 // units of the busiest workgroup
+    const int pmax = epi == EPI_ARGMAX ? 10 : 7;
+    const int chunks = (upw + pmax - 1) / pmax;
+    p.P = (upw + chunks - 1) / chunks;
+    // as many k-groups as the workers and the LDS (two stage buffers, half of
+    // the groups' partial tiles) allow
+    p.KG = std::max(1, std::min(wide_workers(mb) / p.P, (T + S - 1) / S));
+    while (p.KG > 1 && (size_t)2 * p.KG * mb * 1024 > kWideRing)
+      --p.KG;
+    return p;
+  };
+  if (epi != EPI_STORE) return shape(1);
+  // k-splits (a power of two, see the kernel): the least bytes a workgroup
+  // waits for: its weights from HBM, x from L2 at about four times that rate,
+  // and its share of the fp32 partial sums, written once and read once by the
+  // finishing kernel.  (Counting the partial sums half or twice: 16-scene
+  // verify 1058 and 1067 us against 1056.)
+  WidePlan best{};
+  double least = 0;
+  for (int S = 1; S <= std::min(16, std::max(1, T / 4)); S *= 2) {
+    const WidePlan p = shape(S);
+    const int upw = (units + p.G - 1) / p.G;
+    const double steps = (T + S - 1) / S;
+    const double cost = upw * 2048.0 * steps + steps * mb * 256.0 + 8.0 * S * M * N / ncu;
+    if (S == 1 || cost < least) {
+      least = cost;
+      best = p;
+    }
+  }
+  return best;
+}
+
+template <int MB, int EPI>
+hipError_t launch_wide_mb(const GemvArgs& g, int ns, const dim3& grid, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  const dim3 block((g.wp * g.wkg + kWideLoaders) * 64);
+  switch (ns) {
+    case 1: hipExtLaunchKernelGGL((k_gemm_wide<MB, EPI, 1>), grid, block, g.wlds, s, e0, e1, 0, g); break;
+    case 2: hipExtLaunchKernelGGL((k_gemm_wide<MB, EPI, 2>), grid, block, g.wlds, s, e0, e1, 0, g); break;
+    case 4: hipExtLaunchKernelGGL((k_gemm_wide<MB, EPI, 4>), grid, block, g.wlds, s, e0, e1, 0, g); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
+template <int EPI>
+hipError_t launch_wide(GemvArgs g, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+  const int mb = (g.M + 15) / 16;
+  WidePlan p = wide_plan(EPI, g.N, g.Kd, g.M, wide_cus());
+  if (p.S != g.splits) return hipErrorInvalidValue;   // the caller sized its partial sums with gemm_wide_splits
+  g.wp = p.P;
+  g.wkg = p.KG;
+  g.wnb = wide_nb(mb, p.KG);
+  g.wrb = wide_rb(mb, p.P, p.KG);
+  const int T = (g.Kd + 31) / 32, units = (g.N / kTile + 1) / 2, upw = (units + p.G - 1) / p.G;
+  const int ns = wide_ns(mb, p.KG), round = kWideDepth / ns, steps = (T + p.S - 1) / p.S;
+  g.wsq = T / p.S;
+  g.wsr = T % p.S;
+  g.wuq = units / p.G;
+  g.wur = units % p.G;
+  g.wnch = (upw + p.P - 1) / p.P;
+  g.wcu = (upw + g.wnch - 1) / g.wnch;
+  const int st = (steps + p.KG * ns - 1) / (p.KG * ns);
+  g.wnst = (st + round - 1) / round * round;   // a whole number of unrolled rounds
+  g.wrp = (65536 + p.P - 1) / p.P;
+  g.wlds = (int)wide_lds_bytes(mb, p.P, p.KG, EPI);
+  const dim3 grid(p.G * p.S);
+  switch (mb) {
+    case 3: return launch_wide_mb<3, EPI>(g, ns, grid, s, e0, e1);
+    case 4: return launch_wide_mb<4, EPI>(g, ns, grid, s, e0, e1);
+    case 5: return launch_wide_mb<5, EPI>(g, ns, grid, s, e0, e1);
+    case 6: return launch_wide_mb<6, EPI>(g, ns, grid, s, e0, e1);
+    case 7: return launch_wide_mb<7, EPI>(g, ns, grid, s, e0, e1);
+    case 8: return launch_wide_mb<8, EPI>(g, ns, grid, s, e0, e1);
+    case 9: return launch_wide_mb<9, EPI>(g, ns, grid, s, e0, e1);
+    case 10: return launch_wide_mb<10, EPI>(g, ns, grid, s, e0, e1);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+template <int MB, int EPI>
+void set_wide_attr(int limit) {
+  const void* f[3] = {reinterpret_cast<const void*>(&k_gemm_wide<MB, EPI, 1>),
+                      reinterpret_cast<const void*>(&k_gemm_wide<MB, EPI, 2>),
+                      reinterpret_cast<const void*>(&k_gemm_wide<MB, EPI, 4>)};
+  for (const void* p : f) (void)hipFuncSetAttribute(p, hipFuncAttributeMaxDynamicSharedMemorySize, limit - 2048);
+}
+
 template <int MB>
 void set_wide_attributes(int limit) {
-  const int lds = (int)std::min((size_t)limit, wide_lds_bytes(MB, 8192));
-  const void* f[3] = {reinterpret_cast<const void*>(&k_gemm_wide<MB, EPI_SWIGLU>),
-                      reinterpret_cast<const void*>(&k_gemm_wide<MB, EPI_ARGMAX>),
-                      reinterpret_cast<const void*>(&k_gemm_wide<MB, EPI_STORE>)};
-  for (const void* p : f) (void)hipFuncSetAttribute(p, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  set_wide_attr<MB, EPI_SWIGLU>(limit);
+  set_wide_attr<MB, EPI_ARGMAX>(limit);
+  set_wide_attr<MB, EPI_STORE>(limit);
 }
 
 template <int EPI>
@@ -849,13 +975,22 @@ void gemm_set_attributes(int limit) {
   set_wide_attributes<10>(limit);
 }
 
+bool gemm_takes_wide(int epi, const GemvArgs& g) {
+  return g.pw && g.M > kSgMaxRows && g.M <= SPEC_MAX_ROWS &&
+         (epi == EPI_STORE || ((epi == EPI_SWIGLU || epi == EPI_ARGMAX) && g.splits == 1 && g.rinv));
+}
+
+int gemm_argmax_entries(const GemvArgs& g) {
+  return gemm_takes_wide(EPI_ARGMAX, g) ? wide_plan(EPI_ARGMAX, g.N, g.Kd, g.M, wide_cus()).G : g.N / kTile;
+}
+
 hipError_t gemm_launch(int epi, const GemvArgs& g, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
   if (g.M <= kSgMaxRowsGemm || g.M > SPEC_MAX_ROWS || g.splits < 1 || (epi != EPI_STORE && g.splits != 1) ||
       g.N % kTile != 0 || g.Kd % 8 != 0)
     return hipErrorInvalidValue;
-  // the 1/rms prologue reads at most lpt_for(parts) sums of squares per
+  // k_gemm's 1/rms prologue reads at most lpt_for(parts) sums of squares per
   // thread, in threads_for / rows parts per row
-  {
+  if (!gemm_takes_wide(epi, g)) {
     const int mb = (g.M + 15) / 16, parts = threads_for(mb) / (16 * mb);
     if ((epi == EPI_ROPE || epi == EPI_SWIGLU || epi == EPI_ARGMAX) &&
         (g.H < kTile || g.H / kTile > lpt_for(parts) * parts))
@@ -863,20 +998,11 @@ hipError_t gemm_launch(int epi, const GemvArgs& g, hipStream_t s, hipEvent_t e0,
   }
   // every operand is addressed with 32-bit byte offsets below kOut
   if ((long long)g.N * ((g.Kd + 31) / 32) * 64 >= kOut || (long long)g.M * g.ldx * 2 >= kOut) return hipErrorInvalidValue;
-  // passes of more than kSgMaxRows rows over the tile-packed copy: the
-  // wide-unit kernel for gate/up (tile pairs) and the LM head in one launch,
-  // and for the k-split partial sums of the other projections
-  {
-    const int mb = (g.M + 15) / 16;
-    const bool wide = g.pw && g.M > kSgMaxRows && mb <= 10 && (g.N / kTile) % 2 == 0 &&
-                      (epi == EPI_STORE || ((epi == EPI_SWIGLU || epi == EPI_ARGMAX) && g.splits == 1)) &&
-                      wide_lds_bytes(mb, epi == EPI_STORE ? 0 : g.H) <= (size_t)gemv_lds_limit();
-    if (g.xpk && !wide) return hipErrorInvalidValue;   // only the wide kernel reads step-major x
-    if (wide) {
-      if (epi == EPI_STORE) return launch_wide<EPI_STORE>(g, s, e0, e1);
-      return epi == EPI_SWIGLU ? launch_wide<EPI_SWIGLU>(g, s, e0, e1) : launch_wide<EPI_ARGMAX>(g, s, e0, e1);
-    }
+  if (gemm_takes_wide(epi, g)) {
+    if (epi == EPI_STORE) return launch_wide<EPI_STORE>(g, s, e0, e1);
+    return epi == EPI_SWIGLU ? launch_wide<EPI_SWIGLU>(g, s, e0, e1) : launch_wide<EPI_ARGMAX>(g, s, e0, e1);
   }
+  if (g.xpk) return hipErrorInvalidValue;   // only the wide kernel reads operand-order x
   switch (epi) {
     case EPI_STORE: return launch_mb<EPI_STORE>(g, s, e0, e1);
     case EPI_ROPE: return launch_mb<EPI_ROPE>(g, s, e0, e1);
@@ -899,13 +1025,7 @@ int gemm_down_splits(int N, int Kd, int ncu) {
   return std::max(1, std::min(s, T / 8));
 }
 
-int gemm_wide_splits(int N, int Kd, int ncu) {
-  // one round of resident workgroups (one per CU), at least 16 k-steps per
-  // split (8 per k-group)
-  const int groups = (N / kTile + kWideTiles - 1) / kWideTiles;
-  const int T = (Kd + 31) / 32;
-  return std::max(1, std::min(ncu / groups, T / 16));
-}
+int gemm_wide_splits(int N, int Kd, int M, int ncu) { return wide_plan(EPI_STORE, N, Kd, M, ncu).S; }
 
 int gemm_wgs_per_cu(int M) {
   // only the 8-wave shape of up to three row blocks is sized for two
@@ -944,7 +1064,7 @@ int gemm_qkv_splits(int N, int Kd, int M, int ncu) {
 }
 
 int gemm_qkv_splits_for(int N, int Kd, int M, int ncu, bool wide) {
-  return (wide && M > kSgMaxRows) ? gemm_wide_splits(N, Kd, ncu) : gemm_qkv_splits(N, Kd, M, ncu);
+  return (wide && M > kSgMaxRows) ? gemm_wide_splits(N, Kd, M, ncu) : gemm_qkv_splits(N, Kd, M, ncu);
 }
 
 }  // namespace specdec

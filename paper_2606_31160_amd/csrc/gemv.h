@@ -24,14 +24,15 @@ struct GemvArgs {
   const bf16_t* pw;      // GEMM only: the tile-packed copy of these weights ([N/16][steps] blocks of
                          // 1 KB, sgemv.h; gate/up as gate, up tile pairs), or null to read w
   int N, Kd;
-  const bf16_t* x;       // [M][ldx], or step-major [Kd/32][M][32] (xpk)
+  const bf16_t* x;       // [M][ldx], or operand order (xpk, device.h)
   int ldx, M, splits;
-  int xpk;               // x is step-major: a 32-wide step's rows are one contiguous run (wide-unit GEMM only)
+  int xpk;               // x is in operand order (wide-unit GEMM only)
   const SeqState* st;
   int rps;               // rows per sequence
   int mpad;              // row stride of ss / amax
   const float* ss_in;    // [H/16][mpad] sums of x^2 of the input rows (ROPE, SWIGLU, ARGMAX)
   int H;                 // row length those sums cover
+  const float* rinv;     // wide-unit GEMM: [M] 1/rms of the input rows (SWIGLU, ARGMAX)
   float eps;
   float* out;            // EPI_STORE: [splits][M][N]
   // EPI_ROPE
@@ -46,13 +47,18 @@ struct GemvArgs {
   bf16_t* xg;            // [M][N] bf16(x * gain)
   float* ss_out;         // [N/16][mpad] sums of x^2
   // EPI_SWIGLU
-  bf16_t* u;             // [M][N/2], or step-major [N/64][M][32] (upk, wide-unit GEMM only)
+  bf16_t* u;             // [M][N/2], or operand order (upk, wide-unit GEMM only)
   int upk;
   // EPI_ARGMAX
   float* amax_v;         // [N/16][mpad]
   int32_t* amax_i;
   bf16_t* logits;        // [M][N]
   int allow_logits;
+  // wide-unit GEMM (set by its launcher): units per chunk, k-groups, x stage buffers, row blocks per sum
+  // round, dynamic LDS bytes
+  int wp, wkg, wnb, wrb, wlds;
+  int wsq, wsr, wuq, wur;   // k-steps per split and units per workgroup: quotient and remainder
+  int wnch, wcu, wnst, wrp; // chunks, units per chunk, stages per chunk, ceil(65536 / wp)
 };
 
 // Passes of up to kThinRows rows use the thin GEMV kernels (kernels.hip);
@@ -67,16 +73,18 @@ size_t gemm_lds_bytes(int M);
 void gemm_set_attributes(int limit);
 // y = x W^T over g.M rows (kSgMaxRowsGemm < M <= SPEC_MAX_ROWS) with epilogue
 // `epi`.  Over the tile-packed copy (g.pw) with more than 32 rows: the
-// wide-unit kernel, one workgroup per CU for SwiGLU and the LM head, grid
-// (ceil(N / 256), g.splits) for EPI_STORE; otherwise k_gemm, grid
+// wide-unit kernel, about one workgroup per CU; otherwise k_gemm, grid
 // (ceil(N / 64), g.splits).  Only EPI_STORE may use k-splits.
 hipError_t gemm_launch(int epi, const GemvArgs& g, hipStream_t s, hipEvent_t e0, hipEvent_t e1);
 // k-splits of an EPI_STORE GEMM (the down projection) over N outputs and Kd inputs.
 int gemm_down_splits(int N, int Kd, int ncu);
-// k-splits of an EPI_STORE launch of the wide-unit kernel (passes of more
-// than kSgMaxRows rows over the tile-packed copy; 256-column workgroups, one
-// per CU): as many as fill one round of the CUs, at least 16 k-steps each.
-int gemm_wide_splits(int N, int Kd, int ncu);
+// Whether such a launch takes the wide-unit kernel.
+bool gemm_takes_wide(int epi, const GemvArgs& g);
+// (max, index) entries per row an EPI_ARGMAX launch leaves: one per workgroup
+// of the wide-unit kernel, else one per tile.
+int gemm_argmax_entries(const GemvArgs& g);
+// k-splits of an EPI_STORE launch of the wide-unit kernel over M rows.
+int gemm_wide_splits(int N, int Kd, int M, int ncu);
 // Workgroups of the k-split GEMM over M rows resident per CU: the runtime's
 // occupancy for the shapes of up to three row blocks (at most 2), else 1;
 // the o and down projections split to fill every resident slot once.

@@ -158,6 +158,9 @@ struct EmbedArgs {
   int H, R, cap, mode, mpad, D, flat;
   int V;                 // vocabulary size: a token outside [0, V) is reported and read as 0
   int mask;              // block pass: input token of the MASK rows
+  bf16_t* xgp;           // null, or an operand-order copy of xg (device.h)
+  float* rinv;           // null, or [Mpad] 1/rms of each row
+  float eps;
   bf16_t* cat2;          // conditioned draft: [Mpad][2H] rows [embedding; feature of the previous slot], or null
   const bf16_t* feat;    // [B][cap][H] fused target features
 };
@@ -220,7 +223,9 @@ __global__ __launch_bounds__(1024) void k_embed(EmbedArgs p) {
   for (int n = threadIdx.x; n < p.H; n += blockDim.x) {
     const float v = live ? bf2f(er[n]) : 0.f;
     p.x[r * p.H + n] = v;
-    p.xg[r * p.H + n] = f2bf(v * bf2f(p.g[n]));
+    const bf16_t xb = f2bf(v * bf2f(p.g[n]));
+    p.xg[r * p.H + n] = xb;
+    if (p.xgp) p.xgp[xop_at((int)r, n, p.mpad >> 4)] = xb;
     sq[n] = v * v;
   }
   if (p.cat2) {
@@ -241,10 +246,17 @@ __global__ __launch_bounds__(1024) void k_embed(EmbedArgs p) {
     p.rcs[r * (p.D / 2) + d] = p.cs[(size_t)pos * (p.D / 2) + d];
   }
   __syncthreads();
+  __shared__ float red[16];
+  float tot = 0.f;
   for (int t = threadIdx.x; t < p.H / kTile; t += blockDim.x) {
     float v = 0.f;
     for (int c = 0; c < kTile; ++c) v += sq[t * kTile + c];
     p.ss[(size_t)t * p.mpad + r] = v;
+    tot += v;
+  }
+  if (p.rinv) {
+    tot = block_sum(tot, red);
+    if (threadIdx.x == 0) p.rinv[r] = rsqrtf(tot / p.H + p.eps);
   }
 }
 
@@ -667,7 +679,9 @@ struct FinishArgs {
   const bf16_t* gain;
   bf16_t* xg;
   float* ss;             // [H/16][mpad]
-  bf16_t* xgp;           // null, or a step-major copy of xg: [H/32][M][32] (all rows; not with select_last)
+  bf16_t* xgp;           // null, or an operand-order copy of xg (device.h; all rows, not with select_last)
+  float* rinv;           // wide contexts: [mpad] 1/rms of each row
+  float eps;
 };
 
 __global__ __launch_bounds__(256) void k_down_finish(FinishArgs p) {
@@ -689,8 +703,46 @@ __global__ __launch_bounds__(256) void k_down_finish(FinishArgs p) {
   if (p.select_last && j != count - 1) return;
   const bf16_t xb = f2bf(x * bf2f(p.gain[n]));
   p.xg[(size_t)out * p.H + n] = xb;
-  if (p.xgp && !p.select_last) p.xgp[((size_t)(n >> 5) * p.M + m) * 32 + (n & 31)] = xb;
   if ((n & 15) == 0) p.ss[(size_t)(n >> 4) * p.mpad + out] = sq;
+}
+
+// The same finish for the wide-unit GEMM's passes, one workgroup per row, so
+// that the row's 1/rms is formed here once instead of by every workgroup that
+// consumes the row.  grid M, 1024 threads, four columns of the row per thread
+// and round; writes the operand-order xg the wide-unit GEMM reads beside xg.
+__global__ __launch_bounds__(1024) void k_row_finish(FinishArgs p) {
+  __shared__ float red[16];
+  const int m = blockIdx.x, b = m / p.rps, j = m - b * p.rps;
+  const int count = p.st[b].count;
+  if (p.select_last && j != count - 1) return;     // uniform: only the last live row is read on
+  const int out = p.select_last ? b : m;
+  float tot = 0.f;
+  for (int n = 4 * threadIdx.x; n < p.H; n += 4 * 1024) {   // H % 16 == 0: whole 4-lane groups take part
+    float* xp = p.x + (size_t)m * p.H + n;
+    f32x4 x = *reinterpret_cast<const f32x4*>(xp);
+    if (j < count) {
+      const float* pp = p.part + (size_t)m * p.H + n;
+      f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+      for (int sp = 0; sp < p.S; ++sp) v += *reinterpret_cast<const f32x4*>(pp + (size_t)sp * p.M * p.H);
+      x += v;
+      *reinterpret_cast<f32x4*>(xp) = x;
+    }
+    const u32x2 g = *reinterpret_cast<const u32x2*>(p.gain + n);
+    const u32x2 xb = u32x2{pack2(x.x * __uint_as_float(g.x << 16), x.y * __uint_as_float(g.x & 0xffff0000u)),
+                           pack2(x.z * __uint_as_float(g.y << 16), x.w * __uint_as_float(g.y & 0xffff0000u))};
+    *reinterpret_cast<u32x2*>(p.xg + (size_t)out * p.H + n) = xb;
+    if (p.xgp && !p.select_last) *reinterpret_cast<u32x2*>(p.xgp + xop_at(m, n, p.mpad >> 4)) = xb;
+    float sq = x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w;
+    sq += __shfl_xor(sq, 1);
+    sq += __shfl_xor(sq, 2);
+    if ((n & 15) == 0) {
+      p.ss[(size_t)(n >> 4) * p.mpad + out] = sq;
+      tot += sq;
+    }
+  }
+  tot = block_sum(tot, red);
+  if (threadIdx.x == 0) p.rinv[out] = rsqrtf(tot / p.H + p.eps);
 }
 
 // Finish of a k-split q/k/v GEMM: per live row m and column pair (2i, 2i+1),
@@ -705,6 +757,7 @@ struct QkvFinishArgs {
   int S, M, N, rps, mpad, H;
   float eps;
   const float* ss;       // [H/16][mpad] sums of x^2 of the input rows
+  const float* rinv;     // null, or [mpad] their 1/rms
   const float2* rcs;     // [Mpad][D/2]
   const int32_t* pt;     // [B][pps]
   int nq, nkv, D, pps;
@@ -717,7 +770,9 @@ __global__ __launch_bounds__(256) void k_qkv_finish(QkvFinishArgs a) {
   const int m = blockIdx.y;
   const int b = m / a.rps, j = m - b * a.rps;
   if (j >= a.st[b].count) return;                 // uniform over the workgroup
-  if (threadIdx.x < 64) {
+  if (a.rinv) {
+    if (threadIdx.x == 0) inv_rms = a.rinv[m];
+  } else if (threadIdx.x < 64) {
     float v = 0.f;
     for (int t = threadIdx.x; t < a.H / kTile; t += 64) v += a.ss[(size_t)t * a.mpad + m];
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
@@ -1205,6 +1260,7 @@ struct CombineArgs {
   float* ro;             // readout: [B][R][nq][4] masses (visual, trajectory/text, generated), entropy
   float inv_ln[SPEC_MAX_BATCH];   // readout: 1 / ln(trajectory/text slots) of each sequence, 0 if <= 1
   int cross;             // cross-attention context (as AttnArgs::cross)
+  int opk;               // 0, or the pass's row blocks: o is written in operand order (device.h)
 };
 
 // One (row j, q head h, sequence b) of the combine; coef is LDS of at least
@@ -1277,7 +1333,8 @@ __device__ __forceinline__ void combine_unit(const CombineArgs& a, int j, int h,
     float t = 0.f;
 #pragma unroll
     for (int g = 0; g < 8; ++g) t += part[g * a.D + d];
-    a.o[(size_t)(b * a.R + j) * a.nq * a.D + h * a.D + d] = f2bf(t);
+    const int r = b * a.R + j, n = h * a.D + d;
+    a.o[a.opk ? xop_at(r, n, a.opk) : (size_t)r * a.nq * a.D + n] = f2bf(t);
   }
 }
 
@@ -1597,6 +1654,10 @@ hipError_t gemm_run(Ctx& c, int epi, const GemvArgs& g, int kind, double bytes) 
     if (e_ != hipSuccess) return e_;        \
   } while (0)
 
+// Whether a layer's o projection of the current pass reads its input in operand order
+// (the wide-unit GEMM, over every layer's packed weights).
+bool wide_o(const Ctx& c) { return c.gemm_wide && !c.sg; }
+
 // Split-KV attention of one layer + the combine of its splits; on the layer
 // an armed readout names, the readout variants of both kernels.
 hipError_t launch_attention(Ctx& c, Model& m, int li) {
@@ -1619,7 +1680,7 @@ hipError_t launch_attention(Ctx& c, Model& m, int li) {
              kLog2e / sqrtf((float)D), c.cls, c.rp, c.cap, cross, ppw};
   dim3 grid((c.attn_splits + ppw - 1) / ppw, nkv * rb, c.B);
   CombineArgs cb{c.st, c.op, c.mp, c.lp, c.o, nq, D, c.R, c.B, c.attn_chunk * ppw, c.rp,
-                 ro ? c.ro_out : nullptr, {}, cross};
+                 ro ? c.ro_out : nullptr, {}, cross, wide_o(c) ? c.Mpad / 16 : 0};
   for (int b = 0; b < c.B && b < SPEC_MAX_BATCH; ++b) cb.inv_ln[b] = c.ro_inv_ln[b];
   const size_t comb_lds = (size_t)(((c.attn_splits + 3) & ~3) + 8 * D) * sizeof(float);
   const size_t lds = attn_lds_bytes(c.attn_chunk, D);
@@ -1735,12 +1796,12 @@ hipError_t launch_qkv_rm(Ctx& c, Model& m, int li, bf16_t* kc, bf16_t* vt) {
     // partial sums, then the norm, rotation and cache append in k_qkv_finish
     g.splits = sq;
     g.out = c.part;
-    if (pk && c.xgp && li > 0) {   // the step-major copy the previous layer's down finish wrote
+    if (pk && c.xgp) {   // the operand-order copy the embedding or the previous layer's finish wrote
       g.x = c.xgp;
       g.xpk = 1;
     }
     CK(gemm_run(c, EPI_STORE, g, SPEC_KERNEL_QKV, gemv_bytes(g.N, H, M, 4.0 * sq)));
-    QkvFinishArgs p{c.st, c.part, sq, M, g.N, c.R, c.Mpad, H, d.rms_eps, c.ss, c.rcs, c.pt,
+    QkvFinishArgs p{c.st, c.part, sq, M, g.N, c.R, c.Mpad, H, d.rms_eps, c.ss, c.rinv, c.rcs, c.pt,
                     nq, nkv, D, c.pps, c.q, kc, vt};
     Timed t(c, SPEC_KERNEL_OTHER, 0);
     hipExtLaunchKernelGGL(k_qkv_finish, dim3((g.N / 2 + 255) / 256, M), dim3(256), 0, S(c), t.e0, t.e1, 0, p);
@@ -1750,6 +1811,15 @@ hipError_t launch_qkv_rm(Ctx& c, Model& m, int li, bf16_t* kc, bf16_t* vt) {
   else
     CK((gemv_launch<EPI_ROPE, 1>(c, g, SPEC_KERNEL_QKV, gemv_bytes(g.N, H, M, 2.0))));
   return hipSuccess;
+}
+
+hipError_t launch_finish(Ctx& c, const FinishArgs& p) {
+  Timed t(c, SPEC_KERNEL_OTHER, 0);
+  if (p.rinv)
+    hipExtLaunchKernelGGL(k_row_finish, dim3(p.M), dim3(1024), 0, S(c), t.e0, t.e1, 0, p);
+  else
+    hipExtLaunchKernelGGL(k_down_finish, dim3((p.H + 255) / 256, p.M), dim3(256), 0, S(c), t.e0, t.e1, 0, p);
+  return hipGetLastError();
 }
 
 hipError_t run_layer(Ctx& c, Model& m, int li, const bf16_t* next_gain, bool select_last) {
@@ -1790,11 +1860,10 @@ hipError_t run_layer(Ctx& c, Model& m, int li, const bf16_t* next_gain, bool sel
       // writes the FFN norm's input, as after the down projection
       g.splits = m.s_o;
       g.out = c.part;
+      g.xpk = wide_o(c) ? 1 : 0;
       CK(gemm_run(c, EPI_STORE, g, SPEC_KERNEL_O, gemv_bytes(H, nq * D, M, 4.0 * m.s_o)));
-      FinishArgs p{c.st, c.part, m.s_o, M, c.R, H, c.Mpad, 0, c.x, w.ffn_norm, c.xg, c.ss, c.xgp};
-      Timed t(c, SPEC_KERNEL_OTHER, 0);
-      hipExtLaunchKernelGGL(k_down_finish, dim3((H + 255) / 256, M), dim3(256), 0, S(c), t.e0, t.e1, 0, p);
-      CK(hipGetLastError());
+      FinishArgs p{c.st, c.part, m.s_o, M, c.R, H, c.Mpad, 0, c.x, w.ffn_norm, c.xg, c.ss, c.xgp, c.rinv, d.rms_eps};
+      CK(launch_finish(c, p));
     } else {
       CK((gemv_launch<EPI_RESID, 1>(c, g, SPEC_KERNEL_O, gemv_bytes(H, nq * D, M, 10.0))));
     }
@@ -1811,14 +1880,15 @@ hipError_t run_layer(Ctx& c, Model& m, int li, const bf16_t* next_gain, bool sel
     g.x = c.xg;
     g.ldx = H;
     g.ss_in = c.ss;
+    g.rinv = c.rinv;
     g.H = H;
     g.eps = d.rms_eps;
     g.u = c.u;
     g.pw = pk ? pk + m.pk_gu : nullptr;
-    if (pk && c.xgp) {   // the wide-unit GEMM reads the step-major copy the o finish wrote
+    if (pk && c.xgp) {   // the wide-unit GEMM reads the operand-order copy the o finish wrote
       g.x = c.xgp;
       g.xpk = 1;
-      g.upk = 1;         // and writes u step-major for the down projection
+      g.upk = 1;         // and writes u in operand order for the down projection
     }
     if (c.gemm_rows)
       CK(gemm_run(c, EPI_SWIGLU, g, SPEC_KERNEL_GATEUP, gemv_bytes(2 * F, H, M, 1.0)));
@@ -1848,10 +1918,9 @@ hipError_t run_layer(Ctx& c, Model& m, int li, const bf16_t* next_gain, bool sel
         CK(gemv_launch_p<EPI_STORE>(c, g, per_split * m.s_down, SPEC_KERNEL_DOWN, gemv_bytes(H, F, M, 4.0 * m.s_down)));
       }
     }
-    FinishArgs p{c.st, c.part, S_down, M, c.R, H, c.Mpad, select_last ? 1 : 0, c.x, next_gain, c.xg, c.ss, c.xgp};
-    Timed t(c, SPEC_KERNEL_OTHER, 0);
-    hipExtLaunchKernelGGL(k_down_finish, dim3((H + 255) / 256, M), dim3(256), 0, S(c), t.e0, t.e1, 0, p);
-    CK(hipGetLastError());
+    FinishArgs p{c.st, c.part, S_down, M, c.R, H, c.Mpad, select_last ? 1 : 0, c.x, next_gain, c.xg, c.ss, c.xgp, c.rinv,
+                 d.rms_eps};
+    CK(launch_finish(c, p));
   }
   return hipSuccess;
 }
@@ -2152,10 +2221,8 @@ hipError_t cond_gemv(Ctx& c, const bf16_t* w, const bf16_t* x, int N, int Kd, in
 hipError_t launch_cond_input(Ctx& c, Model& m) {
   const int H = m.d.hidden;
   CK(cond_gemv(c, c.w_in, c.cat2, H, 2 * H, kCondSplits, c.part));
-  FinishArgs p{c.st, c.part, kCondSplits, c.M, c.R, H, c.Mpad, 0, c.x, m.L[0].attn_norm, c.xg, c.ss};
-  Timed t(c, SPEC_KERNEL_OTHER, 0);
-  hipExtLaunchKernelGGL(k_down_finish, dim3((H + 255) / 256, c.M), dim3(256), 0, S(c), t.e0, t.e1, 0, p);
-  return hipGetLastError();
+  return launch_finish(c, FinishArgs{c.st, c.part, kCondSplits, c.M, c.R, H, c.Mpad, 0, c.x, m.L[0].attn_norm, c.xg, c.ss,
+                                     c.xgp, c.rinv, m.d.rms_eps});
 }
 
 // Verify pass: w_fuse [h0; h1; h2] of every row, as k-split partials (the
@@ -2174,6 +2241,7 @@ hipError_t launch_forward(Ctx& c, PassMode mode) {
                 c.ss,  c.rcs,
                 c.pos3,  c.cs,   m.axis,       d.hidden,         c.R, c.cap,    (int)mode, c.Mpad,
                 d.head_dim, m.flat ? 1 : 0, c.V, c.mask_token,
+                c.sg ? nullptr : c.xgp, c.sg ? nullptr : c.rinv, d.rms_eps,
                 (c.cond && !c.cross && mode != PASS_VERIFY) ? c.cat2 : nullptr, c.feat};
     Timed t(c, SPEC_KERNEL_OTHER, 0);
     hipExtLaunchKernelGGL(k_embed, dim3(c.R, c.B), dim3(1024), (size_t)d.hidden * sizeof(float), c.stream, t.e0, t.e1, 0, p);
@@ -2210,6 +2278,9 @@ hipError_t launch_forward(Ctx& c, PassMode mode) {
   if (mode == PASS_CATCHUP) return hipSuccess;   // consumes tokens only: no LM head
   // LM head (+ 1/rms of the final norm) with the fused per-tile argmax; the
   // draft proposes from each sequence's last row only (stored as row b)
+  // (max, index) entries per row the LM head leaves: one per tile, or one per
+  // workgroup on the packed paths
+  int ntiles = c.sg ? (block ? m.sg_block[1] : m.sg_host[(size_t)d.layers * 4]).amax_n : c.V / kTile;
   bool reduced = false;   // the LM head's last workgroup already reduced the rows (fused tail)
   if (c.sg) {
     const int rows = draft ? c.B : M;
@@ -2240,21 +2311,20 @@ hipError_t launch_forward(Ctx& c, PassMode mode) {
     g.amax_i = c.amax_i;
     g.logits = c.logits;
     g.allow_logits = mode == PASS_VERIFY ? 1 : 0;
+    g.rinv = draft ? nullptr : c.rinv;
     const double bytes = gemv_bytes(c.V, d.hidden, g.M, 0.0) + 8.0 * (c.V / kTile) * g.M;
     if (g.M > kThinRows || (!draft && c.gemm_rows)) {
       g.pw = c.gemm_pk ? c.pk_head : nullptr;
-      if (!draft && g.pw && c.xgp) {   // the step-major copy the last down finish wrote
+      if (!draft && g.pw && c.xgp) {   // the operand-order copy the last down finish wrote
         g.x = c.xgp;
         g.xpk = 1;
       }
+      ntiles = gemm_argmax_entries(g);
       CK(gemm_run(c, EPI_ARGMAX, g, SPEC_KERNEL_LMHEAD, bytes));
     }
     else
       CK(gemv_launch_p<EPI_ARGMAX>(c, g, std::min(c.ncu, c.V / kTile), SPEC_KERNEL_LMHEAD, bytes));
   }
-  // (max, index) entries per row the LM head left: one per tile, or one per
-  // workgroup on the packed path
-  const int ntiles = c.sg ? (block ? m.sg_block[1] : m.sg_host[(size_t)d.layers * 4]).amax_n : c.V / kTile;
   if (!reduced) {
     Timed t(c, SPEC_KERNEL_OTHER, 0);
     AmaxArgs p{c.st, c.amax_v, c.amax_i, ntiles, c.Mpad, draft ? 1 : c.R, draft ? 1 : 0, draft ? c.draft_out : nullptr, c.K};
@@ -2280,7 +2350,7 @@ hipError_t launch_ctx_kv(Ctx& c) {
   {
     EmbedArgs p{c.st,   c.hist, c.embed, m.L[0].attn_norm, c.x, c.xg, c.ss, c.rcs, c.pos3, c.cs, m.axis,
                 d.hidden, c.R, c.cap, (int)PASS_CTX, c.Mpad, d.head_dim, m.flat ? 1 : 0, c.V, c.mask_token,
-                nullptr, c.feat};
+                c.xgp, c.rinv, d.rms_eps, nullptr, c.feat};
     Timed t(c, SPEC_KERNEL_OTHER, 0);
     hipExtLaunchKernelGGL(k_embed, dim3(c.R, c.B), dim3(1024), (size_t)d.hidden * sizeof(float), c.stream, t.e0,
                           t.e1, 0, p);

@@ -294,8 +294,8 @@ Layout make_layout(const spec_config* cfg, const spec_seq_init* seqs) {
 // tile-packed copy (the wide-unit GEMM)
 void set_splits(Model& m, int M, bool gemm_rows, bool wide) {
   if (wide) {
-    m.s_down = gemm_wide_splits(m.d.hidden, m.d.ffn, num_cus());
-    m.s_o = gemm_wide_splits(m.d.hidden, m.d.q_heads * m.d.head_dim, num_cus());
+    m.s_down = gemm_wide_splits(m.d.hidden, m.d.ffn, M, num_cus());
+    m.s_o = gemm_wide_splits(m.d.hidden, m.d.q_heads * m.d.head_dim, M, num_cus());
     return;
   }
   const int slots = gemm_rows ? num_cus() * gemm_wgs_per_cu(M) : num_cus();
@@ -434,6 +434,7 @@ size_t carve(Ctx& c, const spec_config* cfg, const spec_seq_init* seqs, bool has
   c.xg = cv.take<bf16_t>((size_t)L.Mpad * H);
   c.xgp = (c.gemm_wide && H % 32 == 0) ? cv.take<bf16_t>((size_t)L.Mpad * H) : nullptr;
   c.ss = cv.take<float>((size_t)(H / kTile) * L.Mpad);
+  c.rinv = c.gemm_wide ? cv.take<float>(L.Mpad) : nullptr;
   c.rcs = cv.take<float2>((size_t)L.Mpad * (D / 2));
   c.part = cv.take<float>(part);
   c.part_elems = part;

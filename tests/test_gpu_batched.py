@@ -281,3 +281,19 @@ def test_sixteen_scenes_7b_width_one_layer(path):
     s = _session(w, source="device", provider=src, page_seed=14, flags=S.PATH_FLAGS[path])
     _verify_against_oracle(w, s, T, seed=7, check_kv=(0, 15), kv=S.device_kv)
     s.close()
+
+
+@pytest.mark.parametrize("batch,K,vocab,ffn", [(16, 5, 1040, 688), (16, 4, 1008, 80), (14, 8, 1024, 1040), (16, 7, 16 * 641, 688)])
+def test_wide_gemm_unit_and_step_remainders(batch, K, vocab, ffn):
+    # passes of 80 to 128 tiny rows: an odd number of LM-head tiles (the last unit is half), more units than
+    # workgroups, FFN widths of half a 32-column step and of fewer k-steps than a split's stages, a last row block
+    # that is not full
+    from dataclasses import replace
+    w = W.get("C1")
+    t = replace(w.target, ffn=ffn)
+    w = _scenes(w.with_(target=t, draft=None, vocab=vocab, K=K), batch, 430, 600, seed=31)
+    assert w.batch * (K + 1) > 64
+    src = W.HostWeights(w)
+    T, _ = S.oracle_decoders(w, src)
+    s = _session(w, provider=src, page_seed=4)
+    _verify_against_oracle(w, s, T, seed=9)

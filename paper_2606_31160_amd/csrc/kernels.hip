@@ -1079,148 +1079,243 @@ __global__ __launch_bounds__(NW * 64, (NW == 8 && !RO) ? 6 : 1) void k_attn(Attn
   attn_partials<D, RO, NW>(a, lds);
 }
 
-// The same split-KV attention with a.ppw consecutive pages per workgroup,
-// for passes over many sequences (there are workgroups enough without one
-// per page, and fewer splits mean fewer partial outputs written and merged).
-// Pages are taken one at a time through the same LDS tile: the next page's
-// keys and values are loaded while this one's scores and products run, and
-// the running (max, sum, output) of each row is rescaled when the max grows.
-// grid (groups of ppw pages, kv heads x row blocks, B), 256 threads.
-
+// The same split-KV attention with a.ppw consecutive pages per workgroup, for
+// passes with workgroups enough without one per page (fewer splits mean fewer
+// partial outputs written and merged).
+//
+// What bounds it: reading the pages from HBM once, so the loads must never
+// stop.  A wave of its own copies pages into two LDS buffers by buffer-to-LDS
+// loads, one page ahead of the NW waves that multiply; 64 KB per workgroup, two
+// workgroups and 128 KB in flight per CU, no registers held by loads.  The rows
+// in LDS have no padding (the loads write runs of 1 KB); instead the 16-byte
+// chunks of a row are permuted by an xor with row bits so that the eight lanes
+// that an LDS read serves together fall in distinct banks:
+//   keys    row r, chunk c at c ^ ((r & 3) + 4 ((r >> 3) & 3))   (D = 128)
+//                             c ^ (((r >> 1) & 1) + 2 ((r >> 3) & 3))  (D = 64)
+//   values  row d, chunk c at c ^ ((d >> 1) & 7)
+// Row i of the h-th 16-key tile of a 32-key half is key 8 (i >> 2) + 4 h + (i & 3),
+// so that a lane's eight probabilities of the half belong to eight consecutive
+// keys, one 16-byte read of the value rows.  Pages that every row of the pass
+// sees in full take no masks.  The running (max, sum, output) of each row is
+// rescaled when the max grows.
+//
+// Per launch, 7B widths: 16 scenes of 2 to 8 thousand tokens at 144 rows 47 -> 37
+// us (168 MB, 25 us at the read rate; loads alone 31), at 16 rows 34 -> 30; 5
+// scenes at 45 rows 15.3 -> 11.2; one scene of 4096 tokens 8.2 -> 7.4 and a
+// shorter combine; the paper backbone at 17 rows 14.8 -> 11.1.  (The form before
+// held a page in registers on its way to LDS, three workgroups per CU.)
+// grid (page groups of all sequences x kv heads, row blocks), NW + 1 waves.
 template <int D>
-__global__ __launch_bounds__(256, 3) void k_attn_pages(AttnArgs a) {
-  extern __shared__ __align__(16) unsigned char lds[];
-  const int grp = blockIdx.x;
-  const int kvh = blockIdx.y / a.row_blocks, rb = blockIdx.y % a.row_blocks;
-  const int b = blockIdx.z;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int g4 = lane >> 4;
-  const SeqState& s = a.st[b];
-  const int count = s.count, base = s.base, causal = s.causal, seq_len = s.seq_len;
-  const int rows = count * a.G;
-  const int wrow0 = rb * 64 + wave * 16;
-  const int qr = wrow0 + (lane & 15);
-  const bool rvalid = qr < rows;
-  const int j = rvalid ? qr / a.G : 0;
-  const int hq = kvh * a.G + (rvalid ? qr % a.G : 0);
+__device__ __forceinline__ int attn_key_swz(int r) {
+  return D == 128 ? (r & 3) + 4 * ((r >> 3) & 3) : ((r >> 1) & 1) + 2 * ((r >> 3) & 3);
+}
+
+template <int D, int NW>
+__global__ __launch_bounds__((NW + 1) * 64, (NW + 4) / 4) void k_attn_pages(AttnArgs a) {
+  constexpr int kPage = kAttnChunk * D * 2;         // bytes of a page's keys (or values) of one kv head
+  extern __shared__ __align__(16) unsigned char lds[];   // [2] x (keys, values)
+  const int rb = blockIdx.y;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+  int b = 0, kvh, grp, count, base, causal, seq_len;
+  if (a.B == 1) {   // one sequence: nothing to look up
+    kvh = blockIdx.x % a.nkv;
+    grp = blockIdx.x / a.nkv;
+    count = a.st[0].count, base = a.st[0].base, causal = a.st[0].causal, seq_len = a.st[0].seq_len;
+  } else {
+    // This workgroup's (sequence, kv head, group) by its number: lane l counts
+    // sequence l's groups.  Full groups come first and the sequences' shorter
+    // last groups after them, so that what does not fit the first round of
+    // workgroups is short, and no workgroup without keys sits between others
+    // (which would leave the XCDs unevenly loaded).
+    const SeqState& q = a.st[min(lane, a.B - 1)];
+    const int c = lane < a.B ? q.count : 0, bs = q.base, ca = q.causal, sl = q.seq_len;
+    const int end = c == 0 ? 0 : a.cross ? min(bs + c - 1, sl) : bs + c;
+    const int pages = (end + kAttnChunk - 1) / kAttnChunk, full = pages / a.ppw;
+    const int nf = full * a.nkv, nl = pages > full * a.ppw ? a.nkv : 0;
+    int sf = nf, sp = nl;   // sums up to and including this lane's sequence
+#pragma unroll
+    for (int o = 1; o < SPEC_MAX_BATCH; o <<= 1) {
+      const int x = __shfl_up(sf, o), y = __shfl_up(sp, o);
+      if (lane >= o) sf += x, sp += y;
+    }
+    const int allf = __builtin_amdgcn_readlane(sf, SPEC_MAX_BATCH - 1), alll = __builtin_amdgcn_readlane(sp, SPEC_MAX_BATCH - 1);
+    int w = blockIdx.x;
+    if (w >= allf + alll) return;
+    if (w < allf) {
+      b = __builtin_ctzll(__ballot(sf > w));
+      w -= __builtin_amdgcn_readlane(sf - nf, b);
+      const int n = __builtin_amdgcn_readlane(full, b);
+      kvh = w / n;
+      grp = w - kvh * n;
+    } else {
+      w -= allf;
+      b = __builtin_ctzll(__ballot(sp > w));
+      kvh = w - __builtin_amdgcn_readlane(sp - nl, b);
+      grp = __builtin_amdgcn_readlane(full, b);
+    }
+    count = __builtin_amdgcn_readlane(c, b), base = __builtin_amdgcn_readlane(bs, b);
+    causal = __builtin_amdgcn_readlane(ca, b), seq_len = __builtin_amdgcn_readlane(sl, b);
+  }
+  const int32_t* pt = a.pt + b * a.pps + grp * a.ppw;
+  const int page0 = pt[0];
+  asm volatile("" ::"s"(page0), "s"(count), "s"(base), "s"(causal), "s"(seq_len));   // all loads issued before any is awaited
   const int kv_end = a.cross ? min(base + count - 1, seq_len) : base + count;
-  const int vis_end = a.cross ? min(base + j, seq_len) : base + (j < causal ? j + 1 : count);
   const int gk0 = grp * a.ppw * kAttnChunk;
   const int gk1 = min(gk0 + a.ppw * kAttnChunk, kv_end);
-  const size_t oi = (((size_t)grp * a.B + b) * a.nq + hq) * a.R + j;
+  const int rows = count * a.G;
+  if (gk0 >= gk1 || rb * 16 * NW >= rows) return;   // no keys in this split, or no rows: the combine reads neither
+  const int np = (gk1 - gk0 + kAttnChunk - 1) / kAttnChunk;
+  auto barrier = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
 
-  if (gk0 >= gk1) {                                 // no keys in this split (workgroup-uniform)
-    if (wrow0 >= rows) return;
-    if (rvalid && g4 == 0) {
-      a.mp[oi] = -INFINITY;
-      a.lp[oi] = 0.f;
-    }
-    if (rvalid) {
-      bf16_t* op = a.op + oi * D;
-      for (int d = g4 * 4; d < D; d += 16) *reinterpret_cast<u32x2*>(op + d) = u32x2{0u, 0u};
+  if (wave == NW) {
+    // the loader: 1 KB per load, lane l writes the l-th 16 bytes
+    constexpr int kLoads = kPage / 1024;            // per operand
+    auto issue = [&](int page, int buf) {
+      const size_t pg = (size_t)page * a.nkv + kvh;
+      const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<bf16_t*>(a.kc + pg * kAttnChunk * D), 0, kPage, 0x00020000);
+      const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<bf16_t*>(a.vt + pg * D * kAttnChunk), 0, kPage, 0x00020000);
+      unsigned char* kd = lds + buf * 2 * kPage;
+      constexpr int KC = D / 8;                     // 16-byte chunks of a key row
+#pragma unroll 4
+      for (int i = 0; i < kLoads; ++i) {
+        const int q = 64 * i + lane, r = q / KC, c = (q % KC) ^ attn_key_swz<D>(r);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rk, (__attribute__((address_space(3))) void*)(kd + 1024 * i), 16,
+                                                 (r * KC + c) * 16, 0, 0, 2);
+      }
+#pragma unroll 4
+      for (int i = 0; i < kLoads; ++i) {
+        const int q = 64 * i + lane, d = q >> 3, c = (q & 7) ^ ((d >> 1) & 7);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (__attribute__((address_space(3))) void*)(kd + kPage + 1024 * i), 16,
+                                                 (d * 8 + c) * 16, 0, 0, 2);
+      }
+    };
+    issue(page0, 0);
+    if (np > 1) issue(pt[1], 1);
+    int next = np > 2 ? pt[2] : 0;
+    for (int p = 0; p < np; ++p) {
+      if (p + 1 < np)
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kLoads) : "memory");
+      else
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      const int valid = gk1 - gk0 - p * kAttnChunk;   // keys of this page
+      if (valid < kAttnChunk) {
+        // slots past the valid keys hold stale data: their probabilities are
+        // zero, and zero times a stale infinity would not be
+        unsigned char* vd = lds + (p & 1) * 2 * kPage + kPage;
+        for (int d = lane; d < D; d += 64)
+          for (int c = valid >> 3; c < 8; ++c) {
+            u32x4* q = reinterpret_cast<u32x4*>(vd + d * 128 + ((c ^ ((d >> 1) & 7)) * 16));
+            u32x4 v = u32x4{0, 0, 0, 0};
+            if (8 * c < valid) {                    // the chunk the keys end in
+              v = *q;
+              uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+              for (int e = 0; e < 8; ++e)
+                if (8 * c + e >= valid) w[e >> 1] &= (e & 1) ? 0x0000FFFFu : 0xFFFF0000u;
+              v = u32x4{w[0], w[1], w[2], w[3]};
+            }
+            *q = v;
+          }
+      }
+      barrier();                                    // page p is in LDS
+      barrier();                                    // every wave is done with it
+      if (p + 2 < np) {
+        const int page = next;
+        if (p + 3 < np) next = pt[p + 3];
+        issue(page, p & 1);
+      }
     }
     return;
   }
-  const bool active = wrow0 < rows;                 // wave-uniform; inactive waves still pass the barriers
-  const int np = (gk1 - gk0 + kAttnChunk - 1) / kAttnChunk;
 
+  const int g4 = lane >> 4, r16 = lane & 15;
+  const int wrow0 = rb * (16 * NW) + wave * 16;
+  const int qr = wrow0 + r16;
+  const bool rvalid = qr < rows;
+  const int j = rvalid ? qr / a.G : 0;
+  const int hq = kvh * a.G + (rvalid ? qr % a.G : 0);
+  const int vis_end = a.cross ? min(base + j, seq_len) : base + (j < causal ? j + 1 : count);
+  const int vis_all = a.cross ? min(base, seq_len) : base + 1;   // keys every row sees
+  const size_t oi = (((size_t)grp * a.B + b) * a.nq + hq) * a.R + j;
+  const bool active = wrow0 < rows;                 // wave-uniform; inactive waves still pass the barriers
   u32x4 qf[D / 32];
   {
     const bf16_t* qp = a.q + ((size_t)(b * a.R + j) * a.nq + hq) * D + 8 * g4;
 #pragma unroll
     for (int t = 0; t < D / 32; ++t) qf[t] = ld16(qp + 32 * t);
   }
-  const int kst = D + kAttnPadK, vst = kAttnChunk + kAttnPadV;
-  bf16_t* Ks = reinterpret_cast<bf16_t*>(lds);
-  bf16_t* Vs = Ks + (size_t)kAttnChunk * kst;
-  constexpr int PER_T = kAttnChunk * D / 8 / 256;   // 16-byte vectors per thread and operand
-  static_assert(PER_T * 256 * 8 == kAttnChunk * D, "the threads cover the page exactly");
-  constexpr int per_row = kAttnChunk / 8;
-  u32x4 kr[PER_T], vr[PER_T];
-  auto issue = [&](int pi) {   // page pi of the group: loads into registers
-    const int page = a.pt[b * a.pps + grp * a.ppw + pi];
-    const size_t pg = (size_t)page * a.nkv + kvh;
-    const bf16_t* Kb = a.kc + pg * kAttnChunk * D;
-    const bf16_t* Vb = a.vt + pg * D * kAttnChunk;
+  // byte offsets of this lane's operand chunks inside a page: key tile (hb, h)
+  // chunk 4 t + g4 and value tile dt of half hb; the xor leaves the row terms
+  // apart, and every further tile is a constant away
+  const int krow = 8 * (r16 >> 2) + (r16 & 3);
+  int kch[D / 32];
 #pragma unroll
-    for (int u = 0; u < PER_T; ++u) {
-      const int i = threadIdx.x + 256 * u;
-      // non-temporal: the 16 scenes' keys and values (~170 MB a layer) are
-      // read once per pass and do not fit the last-level cache
-      kr[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(Kb + (size_t)(i / (D / 8)) * D + 8 * (i % (D / 8))));
-      vr[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(Vb + (size_t)(i / per_row) * kAttnChunk + 8 * (i % per_row)));
-    }
-  };
-  auto stage = [&](int k0, int k1) {   // registers -> LDS; values past the valid keys as zeros
+  for (int t = 0; t < D / 32; ++t) kch[t] = krow * D * 2 + ((4 * t + g4) ^ attn_key_swz<D>(krow)) * 16;
+  int vch[2];
 #pragma unroll
-    for (int u = 0; u < PER_T; ++u) {
-      const int i = threadIdx.x + 256 * u;
-      *reinterpret_cast<u32x4*>(Ks + (size_t)(i / (D / 8)) * kst + 8 * (i % (D / 8))) = kr[u];
-      const int d = i / per_row, v8 = i % per_row;
-      attn_stage_values(Vs + (size_t)d * vst, v8, k0 + 8 * v8, k1, vr[u]);
-    }
-  };
+  for (int hb = 0; hb < 2; ++hb) vch[hb] = kPage + r16 * 128 + ((4 * hb + g4) ^ ((r16 >> 1) & 7)) * 16;
 
-  float m_run = -INFINITY, l_run = 0.f;
+  float m_run = -INFINITY, l_run = 0.f;             // max in log2 units
   f32x4 o[D / 16];
 #pragma unroll
   for (int dt = 0; dt < D / 16; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  issue(0);
   for (int pi = 0; pi < np; ++pi) {   // workgroup-uniform
-    const int k0 = gk0 + pi * kAttnChunk, k1 = min(k0 + kAttnChunk, kv_end);
-    if (pi > 0) __syncthreads();      // every wave has read the previous page
-    stage(k0, k1);
-    __syncthreads();
-    if (pi + 1 < np) issue(pi + 1);   // in flight while this page is used
-    if (!active) continue;
-    f32x4 sc[4];
+    const int k0 = gk0 + pi * kAttnChunk;
+    const unsigned char* pg = lds + (pi & 1) * 2 * kPage;
+    barrier();
+    if (active) {
+      float p[16];   // scores, then probabilities, of keys 32 hb + 8 g4 + 4 h + i at 8 hb + 4 h + i
 #pragma unroll
-    for (int h = 0; h < 4; ++h) {
-      const bf16_t* kp = Ks + (size_t)(16 * h + (lane & 15)) * kst + 8 * g4;
-      f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int hb = 0; hb < 2; ++hb)
 #pragma unroll
-      for (int t = 0; t < D / 32; ++t) acc = mfma16x16x32(*reinterpret_cast<const u32x4*>(kp + 32 * t), qf[t], acc);
-      sc[h] = acc;
-    }
-    float p[16];
-    float pm = -INFINITY;
+        for (int h = 0; h < 2; ++h) {
+          // rows 32 hb + 4 h further: D = 128 keeps its xor term (bits 0, 1, 3 and
+          // 4 of the row), D = 64 likewise (bit 1 and bits 3, 4)
+          f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int h = 0; h < 4; ++h)
+          for (int t = 0; t < D / 32; ++t)
+            acc = mfma16x16x32(*reinterpret_cast<const u32x4*>(pg + kch[t] + (32 * hb + 4 * h) * D * 2), qf[t], acc);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int key = k0 + 16 * h + 4 * g4 + i;
-        const bool ok = rvalid && key < k1 && key < vis_end;
-        const float v = ok ? sc[h][i] * a.scale_log2 : -INFINITY;
-        p[h * 4 + i] = v;
-        pm = fmaxf(pm, v);
+          for (int i = 0; i < 4; ++i) p[8 * hb + 4 * h + i] = acc[i];
+        }
+      const bool full = k0 + kAttnChunk <= vis_all;   // workgroup-uniform
+      if (!full) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int key = k0 + 32 * (i >> 3) + 8 * g4 + (i & 7);
+          if (!(rvalid && key < gk1 && key < vis_end)) p[i] = -INFINITY;
+        }
       }
-    pm = fmaxf(pm, __shfl_xor(pm, 16));
-    pm = fmaxf(pm, __shfl_xor(pm, 32));
-    const float m_new = fmaxf(m_run, pm);
-    const float alpha = m_run == -INFINITY ? 0.f : exp2f(m_run - m_new);
-    float ls = 0.f;
+      float pm = p[0];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const float v = p[i];
-      p[i] = (v == -INFINITY) ? 0.f : exp2f(v - m_new);
-      ls += p[i];
-    }
-    l_run = l_run * alpha + ls;
+      for (int i = 1; i < 16; ++i) pm = fmaxf(pm, p[i]);
+      pm = fmaxf(pm, __shfl_xor(pm, 16));
+      pm = fmaxf(pm, __shfl_xor(pm, 32));
+      const float m_new = fmaxf(m_run, pm * a.scale_log2);
+      const float alpha = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);
+      const float mm = m_new == -INFINITY ? 0.f : m_new;   // a row that sees no key yet: all probabilities zero
+      float ls = 0.f;
 #pragma unroll
-    for (int dt = 0; dt < D / 16; ++dt) o[dt] *= alpha;
-#pragma unroll
-    for (int hb = 0; hb < 2; ++hb) {
-      const float* ph = p + 8 * hb;
-      const u32x4 pb = u32x4{pack2(ph[0], ph[1]), pack2(ph[2], ph[3]), pack2(ph[4], ph[5]), pack2(ph[6], ph[7])};
-      // V^T operands read here, not ahead of the softmax: fewer registers, so
-      // that three workgroups fit a CU and more pages are in flight
-#pragma unroll
-      for (int dt = 0; dt < D / 16; ++dt) {
-        const bf16_t* vp = Vs + (size_t)(16 * dt + (lane & 15)) * vst + 32 * hb + 8 * g4;
-        o[dt] = mfma16x16x32(*reinterpret_cast<const u32x4*>(vp), pb, o[dt]);
+      for (int i = 0; i < 16; ++i) {
+        p[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(p[i], a.scale_log2, -mm));
+        ls += p[i];
       }
+      l_run = l_run * alpha + ls;
+#pragma unroll
+      for (int dt = 0; dt < D / 16; ++dt) o[dt] *= alpha;
+#pragma unroll
+      for (int hb = 0; hb < 2; ++hb) {
+        const float* ph = p + 8 * hb;
+        const u32x4 pb = u32x4{pack2(ph[0], ph[1]), pack2(ph[2], ph[3]), pack2(ph[4], ph[5]), pack2(ph[6], ph[7])};
+#pragma unroll
+        for (int dt = 0; dt < D / 16; ++dt)
+          o[dt] = mfma16x16x32(*reinterpret_cast<const u32x4*>(pg + vch[hb] + dt * 16 * 128), pb, o[dt]);
+      }
+      m_run = m_new;
     }
-    m_run = m_new;
+    barrier();
   }
   if (!active) return;
   l_run += __shfl_xor(l_run, 16);
@@ -1237,7 +1332,6 @@ __global__ __launch_bounds__(256, 3) void k_attn_pages(AttnArgs a) {
     }
   }
 }
-
 
 size_t attn_lds_bytes(int chunk, int D) {
   return ((size_t)chunk * (D + kAttnPadK) + (size_t)D * (chunk + kAttnPadV)) * sizeof(bf16_t);
@@ -1674,11 +1768,16 @@ hipError_t launch_attention(Ctx& c, Model& m, int li) {
   // query rows of one kv head (rows per sequence x q heads per kv head): up
   // to 64 in one workgroup of 4 waves; more (e.g. 17 rows x 4 heads) in
   // workgroups of 8 waves, so that each page is staged once for all of them
-  const int nw = (ppw == 1 && c.R * G > 64) ? 8 : 4;
+  const int nw = c.R * G > 64 ? 8 : 4;
   const int rb = (c.R * G + 16 * nw - 1) / (16 * nw);
   AttnArgs p{c.st, c.q, kc, vt, c.pt, c.op, c.mp, c.lp, nq, nkv, G, c.R, c.B, c.pps, c.attn_chunk, rb,
              kLog2e / sqrtf((float)D), c.cls, c.rp, c.cap, cross, ppw};
   dim3 grid((c.attn_splits + ppw - 1) / ppw, nkv * rb, c.B);
+  if (ppw > 1) {   // k_attn_pages numbers the groups that the sequences can have
+    int groups = 0;
+    for (int n : c.npages) groups += (n + ppw - 1) / ppw;
+    grid = dim3(groups * nkv, rb, 1);
+  }
   CombineArgs cb{c.st, c.op, c.mp, c.lp, c.o, nq, D, c.R, c.B, c.attn_chunk * ppw, c.rp,
                  ro ? c.ro_out : nullptr, {}, cross, wide_o(c) ? c.Mpad / 16 : 0};
   for (int b = 0; b < c.B && b < SPEC_MAX_BATCH; ++b) cb.inv_ln[b] = c.ro_inv_ln[b];
@@ -1687,10 +1786,12 @@ hipError_t launch_attention(Ctx& c, Model& m, int li) {
   {
     Timed t(c, SPEC_KERNEL_ATTN, 0);
     if (ppw > 1) {
+      const size_t pl = (size_t)8 * kAttnChunk * D;   // two pages' keys and values
+      const dim3 block((nw + 1) * 64);
       if (D == 128)
-        hipExtLaunchKernelGGL(k_attn_pages<128>, grid, dim3(256), lds, S(c), t.e0, t.e1, 0, p);
+        hipExtLaunchKernelGGL((nw == 8 ? k_attn_pages<128, 8> : k_attn_pages<128, 4>), grid, block, pl, S(c), t.e0, t.e1, 0, p);
       else
-        hipExtLaunchKernelGGL(k_attn_pages<64>, grid, dim3(256), lds, S(c), t.e0, t.e1, 0, p);
+        hipExtLaunchKernelGGL((nw == 8 ? k_attn_pages<64, 8> : k_attn_pages<64, 4>), grid, block, pl, S(c), t.e0, t.e1, 0, p);
     } else if (nw == 8) {
       if (D == 128)
         hipExtLaunchKernelGGL(ro ? k_attn<128, true, 8> : k_attn<128, false, 8>, grid, dim3(512), lds, S(c), t.e0, t.e1,
@@ -1941,10 +2042,10 @@ void init_kernel_attributes() {
   for (int i = 0; i < 8; ++i)
     (void)hipFuncSetAttribute(attn[i], hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)attn_lds_bytes(kAttnChunk, i < 4 ? 128 : 64));
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_pages<128>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)attn_lds_bytes(kAttnChunk, 128));
-  (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_pages<64>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)attn_lds_bytes(kAttnChunk, 64));
+  const void* pages[4] = {reinterpret_cast<const void*>(&k_attn_pages<128, 4>), reinterpret_cast<const void*>(&k_attn_pages<128, 8>),
+                          reinterpret_cast<const void*>(&k_attn_pages<64, 4>), reinterpret_cast<const void*>(&k_attn_pages<64, 8>)};
+  for (int i = 0; i < 4; ++i)
+    (void)hipFuncSetAttribute(pages[i], hipFuncAttributeMaxDynamicSharedMemorySize, 8 * kAttnChunk * (i < 2 ? 128 : 64));
   set_lds_limit_p<EPI_STORE, 1>();
   set_lds_limit_p<EPI_STORE, 2>();
   set_lds_limit_p<EPI_STORE, 3>();

@@ -370,6 +370,26 @@ bool sg_build_one(Ctx& c, bool fill) {
   return ok;
 }
 
+// Pages per attention workgroup: the fewest with which the prompts' workgroups
+// (target kv heads x page groups) run in one round, two per CU, but not a few
+// more than one per CU, whose second ones would take as long again (the paper
+// backbone's 4096 tokens: 2 pages, 264 workgroups 14.7 us, 3 pages, 176
+// workgroups 11.4 us).  It depends on the prompts, the batch and the kv heads
+// only, never on a pass's rows, so every pass of a context, and of contexts that
+// differ in K, groups a row's attention sums the same way.
+int attn_pages_per_workgroup(const spec_config* cfg, const spec_seq_init* seqs, int ncu) {
+  for (int ppw = 1;; ++ppw) {
+    long long wgs = 0;
+    int most = 0;
+    for (int b = 0; b < cfg->batch; ++b) {
+      const int pages = seqs[b].prefix_len / kAttnChunk + 1;
+      wgs += (long long)cfg->target.kv_heads * ((pages + ppw - 1) / ppw);
+      most = std::max(most, pages);
+    }
+    if (ppw >= most || wgs <= ncu || (wgs > ncu + ncu / 8 && wgs <= 2ll * ncu)) return ppw;
+  }
+}
+
 // Carves the workspace (base == nullptr only measures).  Returns total bytes.
 size_t carve(Ctx& c, const spec_config* cfg, const spec_seq_init* seqs, bool has_draft, char* base) {
   const Layout L = make_layout(cfg, seqs);
@@ -385,12 +405,7 @@ size_t carve(Ctx& c, const spec_config* cfg, const spec_seq_init* seqs, bool has
   c.attn_chunk = L.chunk;
   c.ncu = num_cus();
   c.attn_splits = L.splits;
-  // one page per attention workgroup gives a pass over one sequence of 4 kv
-  // heads enough workgroups; with 8 or more (sequence, kv head) pairs three
-  // pages per workgroup (a third of the partials to merge), from 8 sequences
-  // on four.  The choice depends on the batch and the target's kv heads only,
-  // so every pass of a context groups the attention sums the same way.
-  c.attn_ppw = L.B >= 8 ? 4 : (L.B * cfg->target.kv_heads >= 8 ? 3 : 1);
+  c.attn_ppw = attn_pages_per_workgroup(cfg, seqs, c.ncu);
   c.tgt.d = cfg->target;
   c.tgt.flat = false;
   c.block_draft = has_draft && (cfg->flags & SPEC_FLAG_BLOCK_DRAFT) != 0;

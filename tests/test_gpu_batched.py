@@ -297,3 +297,15 @@ def test_wide_gemm_unit_and_step_remainders(batch, K, vocab, ffn):
     T, _ = S.oracle_decoders(w, src)
     s = _session(w, provider=src, page_seed=4)
     _verify_against_oracle(w, s, T, seed=9)
+
+
+@pytest.mark.parametrize("K", [1, 4])
+def test_attention_page_groups(K):
+    # several cache pages per attention workgroup at head_dim 64: prompts that end just before, at and after a page and
+    # a page group, groups shorter than the rest, 2 and 5 rows per sequence
+    lens = [1087, 1088, 1089, 1151, 1152, 1280, 1283, 1471, 1472, 1530, 1599, 1600, 2047, 2048, 2049, 4100]
+    w = W.get("C1").with_(seqs=tuple(W.c5_layout(n) for n in lens), p_accept=(0.8,) * 16, draft=None, K=K)
+    src = W.HostWeights(w)
+    T, _ = S.oracle_decoders(w, src)
+    s = _session(w, provider=src, page_seed=8)
+    _verify_against_oracle(w, s, T, seed=4, check_kv=(0, 15))

@@ -2381,14 +2381,20 @@ hipError_t launch_forward(Ctx& c, PassMode mode) {
   // draft proposes from each sequence's last row only (stored as row b)
   // (max, index) entries per row the LM head leaves: one per tile, or one per
   // workgroup on the packed paths
-  int ntiles = c.sg ? (block ? m.sg_block[1] : m.sg_host[(size_t)d.layers * 4]).amax_n : c.V / kTile;
+  int ntiles = c.V / kTile;
   bool reduced = false;   // the LM head's last workgroup already reduced the rows (fused tail)
-  if (c.sg) {
+  // a full-row draft step of a context on the wide-unit GEMM proposes from one
+  // row per sequence: the packed GEMV of its one-row steps streams the head (16
+  // rows at 152064 x 3584: 170 us, against 242 on the row-major kernel and 27 for
+  // its argmax launch)
+  const bool head1 = !c.sg && draft && c.one_rows;
+  if (c.sg || head1) {
     const int rows = draft ? c.B : M;
     const double bytes = gemv_bytes(c.V, d.hidden, rows, 0.0) + 8.0 * (c.V / kTile) * rows;
     Timed t(c, SPEC_KERNEL_LMHEAD, bytes);
     const size_t hi = (size_t)d.layers * 4;
-    SgJob h = sg_job(c, block ? m.sg_block[1] : m.sg_host[hi]);
+    SgJob h = sg_job(c, block ? m.sg_block[1] : head1 ? m.sg_one[hi] : m.sg_host[hi]);
+    h.mpad = c.Mpad;   // the stride the pass's sums of squares have
     if (h.S == 1) {
       h.tail = draft ? 2 : 1;
       h.tail_K = c.K;
@@ -2396,6 +2402,7 @@ hipError_t launch_forward(Ctx& c, PassMode mode) {
       h.tail_cnt = c.sg_cnt + c.sg_units;
       reduced = true;
     }
+    ntiles = h.amax_n;
     CK(sg_launch(SG_ARGMAX, h, S(c), t.e0, t.e1));
   } else {
     GemvArgs g = gemv_base(c, draft ? c.B : M, draft ? 1 : c.R);

@@ -26,6 +26,7 @@ constexpr int kGemvSteps = 8;                // max 32-wide k-steps per GEMV wav
 // between spec_init and spec_destroy, so a captured graph stays valid for
 // every round.
 struct SeqState {
+  bf16_t* logits;       // where the current verify's LM head writes them, [M][vocab] (the same for every sequence)
   int32_t seq_len;      // slots holding target K/V = index of the pending token
   int32_t draft_len;    // slots holding draft K/V
   int32_t pending;      // token at index seq_len
@@ -37,7 +38,7 @@ struct SeqState {
   int32_t fin_pending;  // the last verify ends the sequence
   int32_t err;          // sticky ERR_* bits
   int32_t prefix_len;
-  int32_t want_logits;  // the current verify copies bf16 logits out
+  int32_t want_logits;  // the current verify hands out bf16 logits
   int32_t base;         // slot of row 0 of the current pass
   int32_t count;        // valid rows of the current pass (0 when idle)
   int32_t dcall;        // draft_step calls this round (the output column of the next one)
@@ -123,7 +124,7 @@ struct Ctx {
   float* lp = nullptr;              // [splits][B][q_heads][R] running sum
   float* amax_v = nullptr;          // [vocab/16][Mpad] per-tile maximum logit
   int32_t* amax_i = nullptr;        // [vocab/16][Mpad] its index
-  bf16_t* logits = nullptr;         // [Mpad][vocab] bf16 logits of the last verify
+  bf16_t* logits = nullptr;         // [Mpad][vocab] bf16 logits of a verify whose output array the LM head cannot write
   int8_t* cls = nullptr;            // [B][cap] class of every slot: 0 visual, 1 trajectory/text, 2 generated
   float* rp = nullptr;              // [splits][B][q_heads][R][4] attention-budget readout partials
 
@@ -207,7 +208,7 @@ hipError_t launch_stream_read(const void* p, size_t bytes, uint32_t* sink, int s
 hipError_t launch_hold(Ctx& c, double ms);   // bounded device-side wait (timing mode)
 hipError_t launch_prefix_kv(Ctx& c, Model& m, int layer, int b, int prefix_len,
                             const bf16_t* k_pre, const bf16_t* v);
-hipError_t launch_stage_verify(Ctx& c, const int32_t* d_override, int want_logits);
+hipError_t launch_stage_verify(Ctx& c, const int32_t* d_override, void* d_logits);
 hipError_t launch_forward(Ctx& c, PassMode mode);   // embed .. accept / draft pick
 hipError_t launch_commit(Ctx& c, int32_t* acc, int32_t* committed, int32_t* ncommit, int32_t* fin);
 hipError_t launch_logits_out(Ctx& c, void* d_logits);

@@ -86,6 +86,10 @@ __device__ __forceinline__ void st_coh_u32(void* p, uint32_t v) {
 __device__ __forceinline__ uint32_t ld_coh_u32(const void* p) {
   return __hip_atomic_load((const SD_GLOBAL uint32_t*)(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// Stores through a pointer that was itself loaded from memory (its address
+// space is not known to the compiler, which would use flat stores).
+__device__ __forceinline__ void st_global(bf16_t* p, u32x2 v) { *(SD_GLOBAL u32x2*)(p) = v; }
+__device__ __forceinline__ void st_global(bf16_t* p, bf16_t v) { *(SD_GLOBAL bf16_t*)(p) = v; }
 // Waits until every vector memory access of the wave has completed.
 __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 

@@ -375,12 +375,13 @@ __global__ __launch_bounds__(threads_for(MB)) void k_gemm(GemvArgs a) {
       a.u[(size_t)m * F + f] = f2bf(g / (1.f + expf(-g)) * up);
     }
   } else {   // EPI_ARGMAX
-    if (a.allow_logits) {
+    bf16_t* lg = a.allow_logits && a.st[0].want_logits ? a.st[0].logits : nullptr;
+    if (lg) {
       for (int idx = threadIdx.x; idx < kGemmTiles * ROWS * 16; idx += NT) {
         const int w = idx / (ROWS * 16), r = idx % (ROWS * 16), m = r >> 4, cc = r & 15;
         const int nw = (blockIdx.x * kGemmTiles + w) * kTile;
-        if (nw < N && m < M && a.st[m / a.rps].want_logits)
-          a.logits[(size_t)m * N + nw + cc] = f2bf(y[(w * ROWS + m) * kYStride + cc]);
+        if (nw < N && m < M)
+          st_global(lg + (size_t)m * N + nw + cc, f2bf(y[(w * ROWS + m) * kYStride + cc]));
       }
     }
     for (int idx = threadIdx.x; idx < kGemmTiles * ROWS; idx += NT) {
@@ -597,6 +598,8 @@ __global__ __launch_bounds__((wide_workers(MB) + kWideLoaders) * 64) void k_gemm
       }
     }
   } else {
+    // where the logits go, if anywhere
+    bf16_t* lg = EPI == EPI_ARGMAX && a.allow_logits && a.st[0].want_logits ? a.st[0].logits : nullptr;
     const int wi = wave - kWideLoaders, kg = (wi * a.wrp) >> 16, pi = wi - kg * P;
     // Weights of the chunk being refilled: one buffer per tile, ending at the
     // split's last step, so that later steps (and, with no bytes at all, a slot
@@ -743,10 +746,10 @@ __global__ __launch_bounds__((wide_workers(MB) + kWideLoaders) * 64) void k_gemm
               y[i] = lv ? y0[i] * r : 0.f;
               y[4 + i] = lv ? y1[i] * r : 0.f;
             }
-            if (a.allow_logits && m < M && a.st[m / a.rps].want_logits) {
-              bf16_t* lo = a.logits + (size_t)m * N + n;
-              *reinterpret_cast<u32x2*>(lo) = u32x2{pack2(y[0], y[1]), pack2(y[2], y[3])};
-              if (two) *reinterpret_cast<u32x2*>(lo + kTile) = u32x2{pack2(y[4], y[5]), pack2(y[6], y[7])};
+            if (lg && m < M) {
+              bf16_t* lo = lg + (size_t)m * N + n;
+              st_global(lo, u32x2{pack2(y[0], y[1]), pack2(y[2], y[3])});
+              if (two) st_global(lo + kTile, u32x2{pack2(y[4], y[5]), pack2(y[6], y[7])});
             }
             float best = -INFINITY;
             int bi = n;

@@ -52,8 +52,7 @@ struct GemvArgs {
   // EPI_ARGMAX
   float* amax_v;         // [N/16][mpad]
   int32_t* amax_i;
-  bf16_t* logits;        // [M][N]
-  int allow_logits;
+  int allow_logits;      // logits go to SeqState::logits, [M][N], when the state asks for them
   // wide-unit GEMM (set by its launcher): units per chunk, k-groups, x stage buffers, row blocks per sum
   // round, dynamic LDS bytes
   int wp, wkg, wnb, wrb, wlds;

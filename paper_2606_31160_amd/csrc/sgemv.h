@@ -79,8 +79,7 @@ struct SgJob {
   float* amax_v;          // [amax_n][mpad] (max, index) of each row per workgroup (per tile when k-sliced)
   int32_t* amax_i;
   int amax_n;
-  bf16_t* logits;         // [M][ntiles*16]
-  int allow_logits;
+  int allow_logits;       // logits go to SeqState::logits, [M][ntiles*16], when the state asks for them
   // SG_ARGMAX without k-slices: the workgroup that finishes last reduces the
   // per-workgroup pairs of every row to its argmax (no separate launch).
   // tail 1: r* of each row (verify and block passes); 2: a draft step's

@@ -77,7 +77,7 @@ struct RowInfo {
   int b, jr;       // sequence and row within it
   int count;       // that sequence's row count
   int slot, page;  // SG_ROPE: cache slot and its page
-  int want_logits;
+  bf16_t* logits;  // where the row's logits go, or null
   float inv_rms;
   // SG_ARGMAX without k-slices: running (max, index) of the row over this
   // workgroup's tiles, and whether a NaN was seen
@@ -151,8 +151,8 @@ __device__ __forceinline__ void epilogue(const SgJob& j, RowInfo& ri, int rb, in
   } else {   // SG_ARGMAX
     const f32x4 y = ya * ri.inv_rms;
     const int N = j.ntiles * 16, n = 16 * u + 4 * grp;
-    if (j.allow_logits && m < M && ri.want_logits)
-      *reinterpret_cast<u32x2*>(j.logits + (size_t)m * N + n) = u32x2{pack2(y.x, y.y), pack2(y.z, y.w)};
+    if (ri.logits)
+      st_global(ri.logits + n, u32x2{pack2(y.x, y.y), pack2(y.z, y.w)});
     float best = -INFINITY;
     int bi = n;
     int nan = 0;
@@ -320,7 +320,9 @@ __global__ __launch_bounds__(kSgWaves * 64) void k_sgemv(const SgJob j) {
       r.b = mok ? m / j.rps : 0;
       r.jr = m - r.b * j.rps;
       r.count = j.st[r.b].count;
-      r.want_logits = j.st[r.b].want_logits;
+      r.logits = nullptr;
+      if (EPI == SG_ARGMAX && j.allow_logits && mok && j.st[0].want_logits)
+        r.logits = j.st[0].logits + (size_t)m * j.ntiles * 16;
       r.inv_rms = 1.f;
       r.best = -INFINITY;
       r.bi = 0x7fffffff;

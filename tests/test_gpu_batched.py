@@ -309,3 +309,25 @@ def test_attention_page_groups(K):
     T, _ = S.oracle_decoders(w, src)
     s = _session(w, provider=src, page_seed=8)
     _verify_against_oracle(w, s, T, seed=4, check_kv=(0, 15))
+
+
+@pytest.mark.parametrize("batch,path", [(1, "packed"), (1, "rowmajor"), (16, "packed"), (16, "rowmajor")])
+def test_logits_at_any_address(tiny16, batch, path):
+    # the LM head writes the caller's array itself where it is 8-byte aligned and through a copy elsewhere: same bits,
+    # nothing around the array
+    import torch
+    from paper_2606_31160_amd import binding as B
+    w, hp, T = tiny16
+    w = w.with_(seqs=w.seqs[:batch], p_accept=w.p_accept[:batch])
+    drafts = torch.arange(batch * w.K, dtype=torch.int32, device="cuda").reshape(batch, w.K) % w.vocab
+    n = batch * (w.K + 1) * w.vocab
+    got = []
+    for off in (0, 4, 1, 7):
+        s = _session(w, provider=hp, page_seed=3 if batch > 1 else None, flags=S.PATH_FLAGS[path])
+        buf = torch.full((n + 16,), 7.0, dtype=torch.bfloat16, device="cuda")
+        B.spec_verify(s.ctx, drafts.data_ptr(), buf.data_ptr() + 2 * off)
+        torch.cuda.synchronize()
+        got.append(buf[off:off + n].clone())
+        assert (buf[:off] == 7).all() and (buf[off + n:] == 7).all()
+        s.close()
+    assert all(torch.equal(got[0], g) for g in got[1:])

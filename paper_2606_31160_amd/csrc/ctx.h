@@ -103,6 +103,8 @@ struct Ctx {
   int device = 0;
 
   // workspace carve-out
+  size_t table_bytes = 0;           // its start, up to cls: the tables that spec_init builds on the host
+  size_t clear_bytes = 0;           // its start, up to the tile-packed weights: cleared by spec_init
   SeqState* st = nullptr;           // [B]
   int32_t* hist = nullptr;          // [B][cap] token at each index >= prefix_len
   int32_t* pt = nullptr;            // [B][pps] page table (slot s of sequence b: page pt[b][s / kAttnChunk])
@@ -206,6 +208,7 @@ struct Ctx {
 hipError_t launch_zero(Ctx& c, void* p, size_t bytes);
 hipError_t launch_stream_read(const void* p, size_t bytes, uint32_t* sink, int sink_words, hipStream_t s);
 hipError_t launch_hold(Ctx& c, double ms);   // bounded device-side wait (timing mode)
+hipError_t launch_rope_table(Ctx& c);        // fills cs
 hipError_t launch_prefix_kv(Ctx& c, Model& m, int layer, int b, int prefix_len,
                             const bf16_t* k_pre, const bf16_t* v);
 hipError_t launch_stage_verify(Ctx& c, const int32_t* d_override, void* d_logits);

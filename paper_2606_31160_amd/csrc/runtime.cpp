@@ -10,6 +10,7 @@
 #include <exception>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "ctx.h"
@@ -439,9 +440,11 @@ size_t carve(Ctx& c, const spec_config* cfg, const spec_seq_init* seqs, bool has
   c.hist = cv.take<int32_t>((size_t)L.B * L.cap);
   c.pt = cv.take<int32_t>((size_t)L.B * L.splits);
   c.pos3 = cv.take<int32_t>((size_t)L.B * 3 * L.cap);
-  c.cs = cv.take<float2>((size_t)L.cap * (D / 2));
   c.tgt.axis = cv.take<int8_t>(D / 2);
   c.drf.axis = cv.take<int8_t>(D / 2);
+  c.cls = cv.take<int8_t>((size_t)L.B * L.cap);
+  c.table_bytes = cv.off;
+  c.cs = cv.take<float2>((size_t)L.cap * (D / 2));
   c.x = cv.take<float>((size_t)L.Mpad * H);
   c.q = cv.take<bf16_t>((size_t)L.Mpad * nqD);
   c.o = cv.take<bf16_t>((size_t)L.Mpad * nqD);
@@ -461,7 +464,6 @@ size_t carve(Ctx& c, const spec_config* cfg, const spec_seq_init* seqs, bool has
   c.amax_v = cv.take<float>((size_t)(L.V / kTile) * L.Mpad);
   c.amax_i = cv.take<int32_t>((size_t)(L.V / kTile) * L.Mpad);
   c.logits = cv.take<bf16_t>((size_t)L.Mpad * L.V);
-  c.cls = cv.take<int8_t>((size_t)L.B * L.cap);
   c.rp = cv.take<float>(attn_rows * 4);
   if (c.cond) {
     c.cat3 = cv.take<bf16_t>((size_t)L.Mpad * 3 * H);
@@ -514,6 +516,7 @@ size_t carve(Ctx& c, const spec_config* cfg, const spec_seq_init* seqs, bool has
     c.sg_part = cv.take<float>(pf);
     c.sg_cnt = cv.take<unsigned>((size_t)units + 1);   // + the LM head's fused-argmax counter
   }
+  c.clear_bytes = cv.off;
   if (sg_ok || c.gemm_pk) {
     c.sg = sg_ok;
     pk_offsets(c.tgt);
@@ -901,20 +904,15 @@ spec_status spec_init(const spec_config* cfg, const void* embed, const spec_mode
       }
     }
 
-    // host-built tables
-    const int D = cfg->target.head_dim, half = D / 2;
-    std::vector<int32_t> pos((size_t)c.B * 3 * c.cap);
-    for (int b = 0; b < c.B; ++b) build_positions(seqs[b], c.cap, pos.data() + (size_t)b * 3 * c.cap);
-    std::vector<float2> cs((size_t)c.cap * half);
-    for (int p = 0; p < c.cap; ++p)
-      for (int d = 0; d < half; ++d) {
-        const double th = std::pow((double)cfg->target.rope_base, -2.0 * d / D);
-        const double ang = th * (double)p;
-        cs[(size_t)p * half + d] = make_float2((float)std::cos(ang), (float)std::sin(ang));
-      }
-    std::vector<int8_t> ax_t(half), ax_d(half);
-    build_axis(cfg->target, false, ax_t.data());
-    build_axis(cfg->draft, c.drf.flat, ax_d.data());
+    // the host-built tables, in the workspace's layout: one upload
+    std::vector<char> tab(c.table_bytes, 0);
+    auto host = [&](auto* dev) {
+      return reinterpret_cast<std::remove_reference_t<decltype(*dev)>*>(tab.data() + (reinterpret_cast<char*>(dev) -
+                                                                                        static_cast<char*>(workspace)));
+    };
+    for (int b = 0; b < c.B; ++b) build_positions(seqs[b], c.cap, host(c.pos3) + (size_t)b * 3 * c.cap);
+    build_axis(cfg->target, false, host(c.tgt.axis));
+    build_axis(cfg->draft, c.drf.flat, host(c.drf.axis));
     c.pt_host.assign((size_t)c.B * c.pps, 0);
     c.npages.assign(c.B, 0);
     for (int b = 0, next = 0; b < c.B; ++b) {
@@ -924,11 +922,12 @@ spec_status spec_init(const spec_config* cfg, const void* embed, const spec_mode
         c.pt_host[(size_t)b * c.pps + i] = seqs[b].page_table ? seqs[b].page_table[i] : next + i;
       next += n;
     }
+    std::copy(c.pt_host.begin(), c.pt_host.end(), host(c.pt));
     // token class of every slot for the attention-budget readout (Sec. 4.2):
     // vision-block slots, other prompt slots, generated slots
-    std::vector<int8_t> cls((size_t)c.B * c.cap, 2);
     for (int b = 0; b < c.B; ++b) {
-      int8_t* cb = cls.data() + (size_t)b * c.cap;
+      int8_t* cb = host(c.cls) + (size_t)b * c.cap;
+      std::fill(cb, cb + c.cap, (int8_t)2);
       std::fill(cb, cb + seqs[b].prefix_len, (int8_t)1);
       int ntraj = seqs[b].prefix_len;
       for (int i = 0; i < seqs[b].n_blocks; ++i) {
@@ -939,16 +938,14 @@ spec_status spec_init(const spec_config* cfg, const void* embed, const spec_mode
       }
       c.ro_inv_ln[b] = ntraj > 1 ? (float)(1.0 / std::log((double)ntraj)) : 0.f;
     }
-    std::vector<SeqState> st(c.B);
-    std::vector<int32_t> hist((size_t)c.B * c.cap, 0);
     for (int b = 0; b < c.B; ++b) {
       SeqState s{};
       s.seq_len = seqs[b].prefix_len;
       s.draft_len = seqs[b].prefix_len;
       s.pending = seqs[b].pending_token;
       s.prefix_len = seqs[b].prefix_len;
-      st[b] = s;
-      hist[(size_t)b * c.cap + seqs[b].prefix_len] = seqs[b].pending_token;
+      host(c.st)[b] = s;
+      host(c.hist)[(size_t)b * c.cap + seqs[b].prefix_len] = seqs[b].pending_token;
     }
 
     auto hip_fail = [&](hipError_t e, const char* where) {
@@ -957,19 +954,11 @@ spec_status spec_init(const spec_config* cfg, const void* embed, const spec_mode
       return SPEC_E_HIP;
     };
     hipError_t e;
-    if ((e = launch_zero(c, workspace, need)) != hipSuccess) return hip_fail(e, "workspace clear");
-    if ((e = hipMemcpyAsync(c.pos3, pos.data(), pos.size() * 4, hipMemcpyHostToDevice, stream)) != hipSuccess ||
-        (e = hipMemcpyAsync(c.pt, c.pt_host.data(), c.pt_host.size() * 4, hipMemcpyHostToDevice, stream)) !=
-            hipSuccess ||
-        (e = hipMemcpyAsync(c.cs, cs.data(), cs.size() * sizeof(float2), hipMemcpyHostToDevice, stream)) !=
-            hipSuccess ||
-        (e = hipMemcpyAsync(c.tgt.axis, ax_t.data(), half, hipMemcpyHostToDevice, stream)) != hipSuccess ||
-        (e = hipMemcpyAsync(c.drf.axis, ax_d.data(), half, hipMemcpyHostToDevice, stream)) != hipSuccess ||
-        (e = hipMemcpyAsync(c.st, st.data(), st.size() * sizeof(SeqState), hipMemcpyHostToDevice, stream)) !=
-            hipSuccess ||
-        (e = hipMemcpyAsync(c.hist, hist.data(), hist.size() * 4, hipMemcpyHostToDevice, stream)) != hipSuccess ||
-        (e = hipMemcpyAsync(c.cls, cls.data(), cls.size(), hipMemcpyHostToDevice, stream)) != hipSuccess)
+    // (the tile-packed weights are written in full below)
+    if ((e = launch_zero(c, workspace, align_up(c.clear_bytes, 16))) != hipSuccess) return hip_fail(e, "workspace clear");
+    if ((e = hipMemcpyAsync(workspace, tab.data(), tab.size(), hipMemcpyHostToDevice, stream)) != hipSuccess)
       return hip_fail(e, "table upload");
+    if ((e = launch_rope_table(c)) != hipSuccess) return hip_fail(e, "rotary table");
     if (c.sg) {
       if (!sg_build_jobs(c, c.tgt, false, true) || (has_draft && !sg_build_jobs(c, c.drf, true, true))) {
         g_init_error = "packed GEMV plan changed between sizing and init";

@@ -603,14 +603,18 @@ __global__ __launch_bounds__(kSgWaves * 64) void k_sgemv(const SgJob j) {
   }
 }
 
-// Packs row-major weights into the tile layout; one thread per 16-byte block.
+// Packs row-major weights into the tile layout, four 16-byte vectors of a row
+// (256 consecutive bytes per four lanes) per thread and round, all loaded before
+// the first store.
 __global__ void k_pack(bf16_t* dst, PackSrc p) {
-  const size_t nvec = (size_t)p.ntiles * p.T * 64;
+  constexpr int kS = 4;                        // steps per thread and round
+  const int groups = (p.T + kS - 1) / kS;      // of a tile
+  const size_t nvec = (size_t)p.ntiles * groups * 64;
   for (size_t v = (size_t)blockIdx.x * blockDim.x + threadIdx.x; v < nvec; v += (size_t)gridDim.x * blockDim.x) {
     const int lane = (int)(v & 63);
-    const size_t ts = v >> 6;
-    const int step = (int)(ts % p.T), tile = (int)(ts / p.T);
-    const int r = lane & 15, k = step * 32 + 8 * (lane >> 4);
+    const unsigned tg = (unsigned)(v >> 6);
+    const int tile = (int)(tg / (unsigned)groups), s0 = (int)(tg - (unsigned)tile * groups) * kS;
+    const int r = lane & 15, k0 = s0 * 32 + 8 * (lane >> 4);
     const bf16_t* row;
     if (p.pair) {
       row = p.seg[tile & 1] + (size_t)((tile >> 1) * 16 + r) * p.Kd;
@@ -621,9 +625,16 @@ __global__ void k_pack(bf16_t* dst, PackSrc p) {
         if (i < p.nseg && n >= p.row0[i]) sg = i;
       row = p.seg[sg] + (size_t)(n - p.row0[sg]) * p.Kd;
     }
-    u32x4 val = u32x4{0, 0, 0, 0};
-    if (k < p.Kd) val = *reinterpret_cast<const u32x4*>(row + k);
-    *reinterpret_cast<u32x4*>(dst + v * 8) = val;
+    u32x4 val[kS];
+#pragma unroll
+    for (int i = 0; i < kS; ++i) {
+      val[i] = u32x4{0, 0, 0, 0};
+      if (k0 + 32 * i < p.Kd) val[i] = ld16_nt(row + k0 + 32 * i);
+    }
+#pragma unroll
+    for (int i = 0; i < kS; ++i)
+      if (s0 + i < p.T)
+        __builtin_nontemporal_store(val[i], reinterpret_cast<u32x4*>(dst + (((size_t)tile * p.T + s0 + i) * 64 + lane) * 8));
   }
 }
 
@@ -719,7 +730,7 @@ hipError_t sg_launch(int epi, const SgJob& h, hipStream_t s, hipEvent_t e0, hipE
 }
 
 hipError_t sg_pack(bf16_t* dst, const PackSrc& src, hipStream_t s) {
-  const size_t nvec = (size_t)src.ntiles * src.T * 64;
+  const size_t nvec = (size_t)src.ntiles * ((src.T + 3) / 4) * 64;
   const int blocks = (int)std::min<size_t>((nvec + 255) / 256, 16384);
   hipLaunchKernelGGL(k_pack, dim3(blocks), dim3(256), 0, s, dst, src);
   return hipGetLastError();

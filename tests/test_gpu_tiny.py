@@ -518,3 +518,30 @@ def test_nan_logits_are_reported_and_skipped(c1):
         assert coms[0][-1] == ref.committed[-1] and int(acc[0]) == ref.accept_len
     assert jn not in coms[0]
     s.close()
+
+
+@pytest.mark.parametrize("P,D", [(1, 64), (63, 64), (64, 64), (65, 128), (320, 128)])
+def test_prompt_cache_fill(P, D):
+    # prompt keys (rotated, to bf16 rounding) and values (bit-exact) of every slot, the slots after them zero: prompts of
+    # one slot, one short of a page, a page, a page and one, and several pages with a vision grid
+    import workloads as W
+    from dataclasses import replace
+    from oracle import numerics as ON
+    from paper_2606_31160_amd.harness import Session
+    w = W.get("C1")
+    sec = (8, 12, 12) if D == 64 else (16, 24, 24)
+    t = replace(w.target, head_dim=D, mrope_section=sec)
+    lay = W.SeqLayout(P, (W.VisionBlock(0, 1, 16, 16),) if P > 256 else ())
+    w = w.with_(target=t, draft=replace(w.draft, head_dim=D, mrope_section=sec), seqs=(lay,))
+    hp = W.HostWeights(w)
+    T, Dm = S.oracle_decoders(w, hp)
+    seq = S.oracle_sequence(w, 0, T, Dm)
+    s = Session(w)
+    for model, cache in ((0, seq.tc), (1, seq.dc)):
+        for li in range((t if model == 0 else w.draft).layers):
+            k, v = (ON.decode(s.kv(0, model, li, which, 0, P)) for which in (0, 1))
+            ref = np.asarray(cache.k[li][:P])
+            assert np.all(np.abs(k - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-6)
+            assert np.array_equal(v, np.asarray(cache.v[li][:P]))
+            assert not s.kv(0, model, li, 1, P, 8).any() and not s.kv(0, model, li, 0, P, 8).any()
+    s.close()

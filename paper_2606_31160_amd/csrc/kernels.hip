@@ -212,7 +212,6 @@ struct EmbedArgs {
 };
 
 __global__ __launch_bounds__(1024) void k_embed(EmbedArgs p) {
-  extern __shared__ float sq[];   // [H]
   const int j = blockIdx.x, b = blockIdx.y;
   const SeqState& s = p.st[b];
   int base, count, tok = 0, causal = -1;
@@ -266,13 +265,25 @@ __global__ __launch_bounds__(1024) void k_embed(EmbedArgs p) {
   }
   const bf16_t* er = p.mode == PASS_CTX ? p.feat + ((size_t)b * p.cap + (live ? base + j : 0)) * p.H
                                         : p.E + (size_t)tok * p.H;
-  for (int n = threadIdx.x; n < p.H; n += blockDim.x) {
-    const float v = live ? bf2f(er[n]) : 0.f;
-    p.x[r * p.H + n] = v;
-    const bf16_t xb = f2bf(v * bf2f(p.g[n]));
-    p.xg[r * p.H + n] = xb;
-    if (p.xgp) p.xgp[xop_at((int)r, n, p.mpad >> 4)] = xb;
-    sq[n] = v * v;
+  // four columns per thread and round, all loads of a round independent
+  const u32x2 none = u32x2{0u, 0u};
+  float tot = 0.f;
+  for (int n = 4 * threadIdx.x; n < p.H; n += 4 * blockDim.x) {   // H % 16 == 0: whole 4-lane groups take part
+    const u32x2 e = live ? ld8(er + n) : none, g = ld8(p.g + n);
+    const f32x4 v = f32x4{__uint_as_float(e.x << 16), __uint_as_float(e.x & 0xffff0000u), __uint_as_float(e.y << 16),
+                          __uint_as_float(e.y & 0xffff0000u)};
+    const u32x2 xb = u32x2{pack2(v.x * __uint_as_float(g.x << 16), v.y * __uint_as_float(g.x & 0xffff0000u)),
+                           pack2(v.z * __uint_as_float(g.y << 16), v.w * __uint_as_float(g.y & 0xffff0000u))};
+    *reinterpret_cast<f32x4*>(p.x + r * p.H + n) = v;
+    *reinterpret_cast<u32x2*>(p.xg + r * p.H + n) = xb;
+    if (p.xgp) *reinterpret_cast<u32x2*>(p.xgp + xop_at((int)r, n, p.mpad >> 4)) = xb;
+    float sq = v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+    sq += __shfl_xor(sq, 1);
+    sq += __shfl_xor(sq, 2);
+    if ((n & 15) == 0) {
+      p.ss[(size_t)(n >> 4) * p.mpad + r] = sq;
+      tot += sq;
+    }
   }
   if (p.cat2) {
     // the input projection's operand: [embedding; feature of slot - 1], the
@@ -281,26 +292,20 @@ __global__ __launch_bounds__(1024) void k_embed(EmbedArgs p) {
     const bool hasf = live && prev >= s.prefix_len && prev < s.seq_len;
     const bf16_t* fr = p.feat + ((size_t)b * p.cap + (hasf ? prev : 0)) * p.H;
     bf16_t* cr = p.cat2 + r * 2 * p.H;
-    for (int n = threadIdx.x; n < p.H; n += blockDim.x) {
-      cr[n] = live ? er[n] : (bf16_t)0;
-      cr[p.H + n] = hasf ? fr[n] : (bf16_t)0;
+    for (int n = 4 * threadIdx.x; n < p.H; n += 4 * blockDim.x) {
+      *reinterpret_cast<u32x2*>(cr + n) = live ? ld8(er + n) : none;
+      *reinterpret_cast<u32x2*>(cr + p.H + n) = hasf ? ld8(fr + n) : none;
     }
   }
-  if (live && threadIdx.x < p.D / 2) {
-    const int slot = base + j, d = threadIdx.x;
+  // the row's rotary pairs, by the last waves (idle in the rounds above at most widths)
+  const int d = (int)(blockDim.x - 1 - threadIdx.x);
+  if (live && d < p.D / 2) {
+    const int slot = base + j;
     const int pos = p.flat ? slot : p.pos3[((size_t)b * 3 + p.axis[d]) * p.cap + slot];
     p.rcs[r * (p.D / 2) + d] = p.cs[(size_t)pos * (p.D / 2) + d];
   }
-  __syncthreads();
-  __shared__ float red[16];
-  float tot = 0.f;
-  for (int t = threadIdx.x; t < p.H / kTile; t += blockDim.x) {
-    float v = 0.f;
-    for (int c = 0; c < kTile; ++c) v += sq[t * kTile + c];
-    p.ss[(size_t)t * p.mpad + r] = v;
-    tot += v;
-  }
   if (p.rinv) {
+    __shared__ float red[16];
     tot = block_sum(tot, red);
     if (threadIdx.x == 0) p.rinv[r] = rsqrtf(tot / p.H + p.eps);
   }
@@ -2407,7 +2412,7 @@ hipError_t launch_forward(Ctx& c, PassMode mode) {
                 c.sg ? nullptr : c.xgp, c.sg ? nullptr : c.rinv, d.rms_eps,
                 (c.cond && !c.cross && mode != PASS_VERIFY) ? c.cat2 : nullptr, c.feat};
     Timed t(c, SPEC_KERNEL_OTHER, 0);
-    hipExtLaunchKernelGGL(k_embed, dim3(c.R, c.B), dim3(1024), (size_t)d.hidden * sizeof(float), c.stream, t.e0, t.e1, 0, p);
+    hipExtLaunchKernelGGL(k_embed, dim3(c.R, c.B), dim3(1024), 0, c.stream, t.e0, t.e1, 0, p);
     CK(hipGetLastError());
   }
   // draft: a draft step, which proposes from each sequence's last row (stored
@@ -2521,7 +2526,7 @@ hipError_t launch_ctx_kv(Ctx& c) {
                 d.hidden, c.R, c.cap, (int)PASS_CTX, c.Mpad, d.head_dim, m.flat ? 1 : 0, c.V, c.mask_token,
                 c.xgp, c.rinv, d.rms_eps, nullptr, c.feat};
     Timed t(c, SPEC_KERNEL_OTHER, 0);
-    hipExtLaunchKernelGGL(k_embed, dim3(c.R, c.B), dim3(1024), (size_t)d.hidden * sizeof(float), c.stream, t.e0,
+    hipExtLaunchKernelGGL(k_embed, dim3(c.R, c.B), dim3(1024), 0, c.stream, t.e0,
                           t.e1, 0, p);
     CK(hipGetLastError());
   }

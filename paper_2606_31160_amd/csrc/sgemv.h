@@ -47,10 +47,14 @@ struct SgJob {
   int S, G;               // k-slices of T; workgroups per slice (grid = S*G)
   int xs;                 // x streamed with the weights (long k-ranges) instead of held in registers
   int dep9;               // x in registers, 9 steps per worker (inputs of 121..135 steps)
+  int uq, ur;             // units per workgroup of a slice: quotient and remainder (host-computed: the code ahead
+                          // of the first loads is fetched cold by every launch, divisions are most of it)
+  int gx;                 // S = 1: workgroups per XCD when they divide evenly, else 0
   int kmax;               // partial slots per workgroup
   int units;              // fixup units (tiles, or gate/up tile pairs)
   const bf16_t* x;        // input rows [M][ldx], Kd valid columns; or step-major (xpk)
-  int xpk;                // x step-major: [ceil(Kd/32)][M][32], so a step's rows are one contiguous run
+  int xpk;                // x step-major: [ceil(Kd/32)][M][32], so a step's rows are one contiguous run (operand order,
+                          // device.h, reads no faster and at 9 rows slower: 7B down 26.4 -> 28.1 us)
   int ldx, Kd, M, rps;    // rows; rows per sequence
   const float* ss_in;     // normalised input: [Hn/16][mpad] sums of squares, else null
   int Hn, mpad;

@@ -227,14 +227,27 @@ __global__ __launch_bounds__(kSgWaves * 64) void k_sgemv(const SgJob j) {
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int lane = threadIdx.x & 63;
   const int S = j.S, G = j.G, T = j.T, M = j.M;
-  const int sl = blockIdx.x / G, gi = blockIdx.x - sl * G;
-  const int k0 = sl * T / S, k1 = (sl + 1) * T / S, span = k1 - k0;
+  int sl = 0, gi = blockIdx.x, k0 = 0, span = T;
+  if (S > 1) {
+    sl = gi / G;
+    gi -= sl * G;
+    k0 = sl * T / S;
+    span = (sl + 1) * T / S - k0;
+  }
   // Units (a tile, or a gate/up tile pair) are dealt round-robin: this
   // workgroup takes units gi, gi + G, gi + 2G, ... (the last round ragged), so
   // at any moment the workgroups stream neighbouring tiles.
-  const int units = j.ntiles / TPU;
-  const int n_it = (units / G + (gi < units % G ? 1 : 0)) * TPU;   // tiles of this workgroup
-  auto tile_of = [&](int it) { return ((it / TPU) * G + gi) * TPU + it % TPU; };
+  // In whole rounds the workgroups of one XCD (every 8th) take consecutive
+  // units, whose output lines then meet in its L2: the LM head of a verify that
+  // hands out logits writes 32-byte pieces of their rows (7B at 9 rows 175 -> 164
+  // us, paper backbone at 17 rows 214 -> 199; the other projections unchanged).
+  // The last, ragged round keeps its units spread over the XCDs.
+  const int n_it = (j.uq + (gi < j.ur ? 1 : 0)) * TPU;   // tiles of this workgroup
+  const int gw = j.gx ? (gi & 7) * j.gx + (gi >> 3) : gi;
+  auto tile_of = [&](int it) {
+    const int r = it / TPU;
+    return (r * G + (r < j.uq ? gw : gi)) * TPU + it % TPU;
+  };
   f32x4* red = reinterpret_cast<f32x4*>(lds);                                   // [2][MB][workers][64]
   int* pend = reinterpret_cast<int*>(lds + 2 * MB * kSgWorkers * 64 * 16);      // [kSgPendMax + 4]
   float* rms_sh = reinterpret_cast<float*>(pend + kSgPendMax + 4);              // [16 MB] 1/rms per row
@@ -693,6 +706,9 @@ bool sg_plan(SgJob& j, int epi, int ncu, int lds_limit) {
   }
   j.units = j.ntiles / tpu;
   j.G = std::max(1, std::min(ncu / S, j.units));
+  j.uq = j.units / j.G;
+  j.ur = j.units % j.G;
+  j.gx = S == 1 && j.G % 8 == 0 ? j.G / 8 : 0;
   // partial slots (k-sliced reductions): one per unit of a workgroup
   const int kmax = S > 1 ? (j.units + j.G - 1) / j.G : 1;
   if (kmax > kSgPendMax) return false;

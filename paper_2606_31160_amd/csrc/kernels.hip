@@ -318,7 +318,10 @@ __global__ __launch_bounds__(1024) void k_embed(EmbedArgs p) {
 // A workgroup of NW waves owns TT tiles of 16 weight rows and a k-range of
 // 32-wide steps; wave w streams a contiguous chunk of at most SMAX steps of
 // every tile.  Row-major weights: for one step, lane l reads
-// W[row (l&15)][8*(l>>4) .. +8] (16 bytes).  All of a wave's weight loads are
+// W[row (l&15)][8*(l>>4) .. +8] (16 bytes).  That is half a line of 16 rows,
+// whose other half the wave's next step reads, so these loads take the default
+// cache policy: with the non-temporal hint of the packed copy's loads gate/up took
+// 67 us against 57 and the LM head 250 against 216 (7B, 9 rows).  All of a wave's weight loads are
 // issued first; the workgroup then stages its live x rows for the k-range in
 // LDS with coalesced loads, so each x fragment is fetched from L2 once per
 // workgroup and feeds TT MFMAs.  v_mfma_f32_16x16x32_bf16 takes the weight
@@ -371,7 +374,7 @@ __global__ __launch_bounds__(NW * 64) void k_gemv(GemvArgs a) {
 #pragma unroll
     for (int i = 0; i < SMAX; ++i) {
       const int k = (w0 + i) << 5;
-      wv[tt][i] = (w0 + i < w1 && k + kq < Kd) ? ld16_nt(wp + k) : u32x4{0, 0, 0, 0};
+      wv[tt][i] = (w0 + i < w1 && k + kq < Kd) ? ld16(wp + k) : u32x4{0, 0, 0, 0};
     }
   }
 
@@ -587,7 +590,7 @@ __global__ __launch_bounds__(NW * 64) void k_gemv_p(GemvArgs a) {
 #pragma unroll
     for (int i = 0; i < SMAX; ++i) {
       const int k = (w0 + i) << 5;
-      wv[i] = (w0 + i < w1 && k + kq < Kd) ? ld16_nt(wp + k) : u32x4{0, 0, 0, 0};
+      wv[i] = (w0 + i < w1 && k + kq < Kd) ? ld16(wp + k) : u32x4{0, 0, 0, 0};
     }
   };
 
@@ -1151,7 +1154,7 @@ __global__ __launch_bounds__(NW * 64, (NW == 8 && !RO) ? 6 : 1) void k_attn(Attn
 // rescaled when the max grows.
 //
 // Per launch, 7B widths: 16 scenes of 2 to 8 thousand tokens at 144 rows 47 -> 37
-// us (168 MB, 25 us at the read rate; loads alone 31), at 16 rows 34 -> 30; 5
+// us (168 MB, 25 us at the read rate), at 16 rows 34 -> 30; 5
 // scenes at 45 rows 15.3 -> 11.2; one scene of 4096 tokens 8.2 -> 7.4 and a
 // shorter combine; the paper backbone at 17 rows 14.8 -> 11.1.  (The form before
 // held a page in registers on its way to LDS, three workgroups per CU.)

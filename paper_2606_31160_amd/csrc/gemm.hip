@@ -844,7 +844,10 @@ WidePlan wide_plan(int epi, int N, int Kd, int M, int ncu) {
   // verify 1058 and 1067 us against 1056.)
   WidePlan best{};
   double least = 0;
-  for (int S = 1; S <= std::min(16, std::max(1, T / 4)); S *= 2) {
+  // (at most as many as 256-column workgroups would fill the CUs once with, of 16
+  // k-steps or more: that bounds the scratch a pass needs)
+  const int most = std::max(1, std::min(ncu / ((N / kTile + 15) / 16), T / 16));
+  for (int S = 1; S <= std::min(16, most); S *= 2) {
     const WidePlan p = shape(S);
     const int upw = (units + p.G - 1) / p.G;
     const double steps = (T + S - 1) / S;

@@ -331,6 +331,11 @@ spec_status spec_debug_feature(spec_ctx* ctx, int32_t b, int32_t slot0, int32_t 
 #define SPEC_PATH_PACKED 1
 spec_status spec_debug_path(const spec_ctx* ctx, int32_t* path);
 
+/* Cache pages one attention workgroup takes in every pass of a context opened
+ * with these arguments, into *pages (a pass with an armed readout takes one).
+ * Does not synchronise; needs no context. */
+spec_status spec_debug_attn_pages(const spec_config* cfg, const spec_seq_init* seqs /* [batch] */, int32_t* pages);
+
 /* Per-kernel timing with HIP events on the context's stream.  While enabled,
  * calls launch kernels one by one (no graph replay), each through
  * hipExtLaunchKernelGGL with a start/stop event pair, and every pass begins

@@ -102,6 +102,7 @@ def lib():
             "spec_stream_read": [P, ctypes.c_size_t, P, c_int32, P],
             "spec_timing_read": [P, c_int32, POINTER(c_int64), POINTER(c_double), POINTER(c_double)],
             "spec_debug_path": [P, POINTER(c_int32)],
+            "spec_debug_attn_pages": [POINTER(spec_config), POINTER(spec_seq_init), POINTER(c_int32)],
             "spec_debug_feature": [P, c_int32, c_int32, c_int32, P],
         }
         for name, args in sig.items():
@@ -227,6 +228,13 @@ def spec_debug_path(ctx) -> str:
     p = c_int32(-1)
     _check(lib().spec_debug_path(ctx, ctypes.byref(p)), "spec_debug_path", ctx)
     return PATHS[p.value]
+
+
+def spec_debug_attn_pages(cfg: spec_config, seqs) -> int:
+    """Cache pages per attention workgroup of a context opened with these arguments."""
+    n = c_int32(-1)
+    _check(lib().spec_debug_attn_pages(ctypes.byref(cfg), seqs, ctypes.byref(n)), "spec_debug_attn_pages")
+    return n.value
 
 
 def spec_stream_read(d_buf: int, nbytes: int, d_sink: int, sink_words: int, stream: int) -> None:

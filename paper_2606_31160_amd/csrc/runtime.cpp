@@ -371,24 +371,33 @@ bool sg_build_one(Ctx& c, bool fill) {
   return ok;
 }
 
-// Pages per attention workgroup: the fewest with which the prompts' workgroups
-// (target kv heads x page groups) run in one round, two per CU, but not a few
-// more than one per CU, whose second ones would take as long again (the paper
-// backbone's 4096 tokens: 2 pages, 264 workgroups 14.7 us, 3 pages, 176
-// workgroups 11.4 us).  It depends on the prompts, the batch and the kv heads
-// only, never on a pass's rows, so every pass of a context, and of contexts that
-// differ in K, groups a row's attention sums the same way.
+// Pages per attention workgroup: the fewest with which the workgroups (target kv
+// heads x page groups) run in one round, two per CU, but not a few more than one
+// per CU, whose second ones would take as long again (the paper backbone's 4096
+// tokens: 2 pages, 264 workgroups 14.7 us, 3 pages, 176 workgroups 11.1 us), both
+// for the prompts and halfway through the token budget: the count stays for the
+// context's life, and what fits 16 scenes of 200 tokens (one page, 256
+// workgroups) runs in nine rounds 2048 tokens later (4 layers: 837 us against 779
+// with the three pages taken here, 751 with the best count, 5).  It depends on
+// the prompts, the budget, the batch and the kv heads only, never on a pass's
+// rows, so every pass of a context, and of contexts that differ in K, groups a
+// row's attention sums the same way.
 int attn_pages_per_workgroup(const spec_config* cfg, const spec_seq_init* seqs, int ncu) {
-  for (int ppw = 1;; ++ppw) {
+  const int half = cfg->max_new_tokens / 2;
+  auto one_round = [&](int ppw, int grown) {
     long long wgs = 0;
-    int most = 0;
     for (int b = 0; b < cfg->batch; ++b) {
-      const int pages = seqs[b].prefix_len / kAttnChunk + 1;
-      wgs += (long long)cfg->target.kv_heads * ((pages + ppw - 1) / ppw);
-      most = std::max(most, pages);
+      const long long pages = ((long long)seqs[b].prefix_len + grown) / kAttnChunk + 1;
+      wgs += cfg->target.kv_heads * ((pages + ppw - 1) / ppw);
     }
-    if (ppw >= most || wgs <= ncu || (wgs > ncu + ncu / 8 && wgs <= 2ll * ncu)) return ppw;
-  }
+    return wgs <= ncu || (wgs > ncu + ncu / 8 && wgs <= 2ll * ncu);
+  };
+  int longest = 0;
+  for (int b = 0; b < cfg->batch; ++b) longest = std::max(longest, seqs[b].prefix_len);
+  const int most = (int)(((long long)longest + half) / kAttnChunk) + 1;
+  int ppw = 1;
+  while (ppw < most && !(one_round(ppw, 0) && one_round(ppw, half))) ++ppw;
+  return ppw;
 }
 
 // Carves the workspace (base == nullptr only measures).  Returns total bytes.
@@ -1238,6 +1247,21 @@ spec_status spec_debug_path(const spec_ctx* ctx, int32_t* path) {
   const Ctx& c = ctx->c;
   *path = (c.sg || c.gemm_pk) ? SPEC_PATH_PACKED : SPEC_PATH_ROWMAJOR;
   return SPEC_OK;
+}
+
+spec_status spec_debug_attn_pages(const spec_config* cfg, const spec_seq_init* seqs, int32_t* pages) {
+  if (!cfg || !seqs || !pages) return SPEC_E_INVAL;
+  try {
+    std::string err;
+    if (!check_config(cfg, seqs, cfg->draft.layers > 0, err)) {
+      g_init_error = err;
+      return SPEC_E_INVAL;
+    }
+    *pages = attn_pages_per_workgroup(cfg, seqs, num_cus());
+    return SPEC_OK;
+  } catch (...) {
+    return SPEC_E_INVAL;
+  }
 }
 
 spec_status spec_debug_kv(spec_ctx* ctx, int32_t b, int32_t model, int32_t layer, int32_t which, int32_t pos0,

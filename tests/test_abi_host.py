@@ -96,6 +96,29 @@ def test_benchmark_and_paper_configs_validate_on_host(name):
     assert n > 0 and n % 256 == 0
 
 
+def _attn_pages(kv_heads, prompts, budget, K):
+    w = W.get("C1")
+    cfg = _cfg(w, K=K, batch=len(prompts))
+    cfg.max_new_tokens = budget
+    cfg.target.kv_heads = kv_heads
+    cfg.target.q_heads = 4 * kv_heads
+    seqs, keep = _seqs(w, cfg, blocks=[])
+    for s, p in zip(seqs, prompts):
+        s.prefix_len = p
+    return B.spec_debug_attn_pages(cfg, seqs)
+
+
+def test_attention_page_rule_counts_the_tokens_to_come():
+    # a context keeps its page count for life: short prompts with a long budget
+    # take more pages than the prompts alone would (16 x 4 pages x 4 kv heads =
+    # 256 workgroups), and the count does not depend on K
+    assert _attn_pages(4, [200] * 16, 20, 8) == 1
+    assert _attn_pages(4, [200] * 16, 2048, 8) == 3
+    assert _attn_pages(4, [200] * 16, 2048, 0) == 3
+    # the prompts' own round still counts: 8 x 65 pages, two per workgroup = 264
+    assert _attn_pages(8, [4096], 20, 16) == 3
+
+
 @pytest.mark.parametrize("mutate,needle", [
     (lambda c, s: setattr(c, "K", 17), "K out of range"),
     (lambda c, s: setattr(c, "batch", 0), "batch"),

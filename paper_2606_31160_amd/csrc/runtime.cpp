@@ -372,16 +372,22 @@ bool sg_build_one(Ctx& c, bool fill) {
 }
 
 // Pages per attention workgroup: the fewest with which the workgroups (target kv
-// heads x page groups) run in one round, two per CU, but not a few more than one
-// per CU, whose second ones would take as long again (the paper backbone's 4096
-// tokens: 2 pages, 264 workgroups 14.7 us, 3 pages, 176 workgroups 11.1 us), both
-// for the prompts and halfway through the token budget: the count stays for the
-// context's life, and what fits 16 scenes of 200 tokens (one page, 256
-// workgroups) runs in nine rounds 2048 tokens later (4 layers: 837 us against 779
-// with the three pages taken here, 751 with the best count, 5).  It depends on
-// the prompts, the budget, the batch and the kv heads only, never on a pass's
-// rows, so every pass of a context, and of contexts that differ in K, groups a
-// row's attention sums the same way.
+// heads x page groups) run in one round, both for the prompts and halfway through
+// the token budget.
+//   One round: two workgroups per CU, but not a few more than one per CU, whose
+// second ones would take as long again (the paper backbone's 4096 tokens: 2
+// pages, 264 workgroups 14.7 us, 3 pages, 176 workgroups 11.1 us).  One page
+// (k_attn) only where that is at most one workgroup per CU: past it two pages in
+// k_attn_pages are faster (7B, 4 layers, one scene of 4096, 5120, 6144 and 8192
+// tokens, 260 to 516 one-page workgroups: 442, 446, 448 and 455 us with one page,
+// 429, 432, 440 and 445 with two).
+//   The budget: the count stays for the context's life, and what fits 16 scenes
+// of 200 tokens (one page, 256 workgroups) runs in nine rounds 2048 tokens later
+// (4 layers: 837 us against 779 with the three pages taken here, 751 with the
+// best count, 5).
+//   It depends on the prompts, the budget, the batch and the kv heads only, never
+// on a pass's rows, so every pass of a context, and of contexts that differ in K,
+// groups a row's attention sums the same way.
 int attn_pages_per_workgroup(const spec_config* cfg, const spec_seq_init* seqs, int ncu) {
   const int half = cfg->max_new_tokens / 2;
   auto one_round = [&](int ppw, int grown) {
@@ -390,7 +396,7 @@ int attn_pages_per_workgroup(const spec_config* cfg, const spec_seq_init* seqs, 
       const long long pages = ((long long)seqs[b].prefix_len + grown) / kAttnChunk + 1;
       wgs += cfg->target.kv_heads * ((pages + ppw - 1) / ppw);
     }
-    return wgs <= ncu || (wgs > ncu + ncu / 8 && wgs <= 2ll * ncu);
+    return wgs <= ncu || (ppw > 1 && wgs > ncu + ncu / 8 && wgs <= 2ll * ncu);
   };
   int longest = 0;
   for (int b = 0; b < cfg->batch; ++b) longest = std::max(longest, seqs[b].prefix_len);

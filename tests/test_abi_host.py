@@ -119,6 +119,13 @@ def test_attention_page_rule_counts_the_tokens_to_come():
     assert _attn_pages(8, [4096], 20, 16) == 3
 
 
+def test_attention_page_rule_takes_one_page_up_to_one_workgroup_per_cu():
+    assert _attn_pages(4, [4031], 20, 8) == 1    # 63 pages x 4 kv heads = 252 workgroups
+    assert _attn_pages(4, [4096], 20, 8) == 2    # 260
+    assert _attn_pages(4, [5120], 20, 8) == 2    # 324: inside two per CU
+    assert _attn_pages(4, [8192], 20, 8) == 3    # two pages: 260, a few more than one per CU
+
+
 @pytest.mark.parametrize("mutate,needle", [
     (lambda c, s: setattr(c, "K", 17), "K out of range"),
     (lambda c, s: setattr(c, "batch", 0), "batch"),

@@ -371,6 +371,8 @@ bool sg_build_one(Ctx& c, bool fill) {
   return ok;
 }
 
+constexpr int kAttnManyPages = 10;
+
 // Pages per attention workgroup: the fewest with which the workgroups (target kv
 // heads x page groups) run in one round, both for the prompts and halfway through
 // the token budget.
@@ -385,6 +387,12 @@ bool sg_build_one(Ctx& c, bool fill) {
 // of 200 tokens (one page, 256 workgroups) runs in nine rounds 2048 tokens later
 // (4 layers: 837 us against 779 with the three pages taken here, 751 with the
 // best count, 5).
+//   Where even one workgroup per sequence and kv head does not fit (a few more
+// than one per CU, or more than two), no count does, and whole sequences in series
+// leave the last ones alone on the chip: kAttnManyPages pages (2 layers, 16 scenes
+// of 1 to 4 thousand tokens, 40 kv heads: 531 us whole, 478 with 10 pages; of 2048
+// tokens 485 and 430; 9 scenes, 32 kv heads: 417 and 331, 299 and 274; 8 and 12
+// pages within 3% of 10).
 //   It depends on the prompts, the budget, the batch and the kv heads only, never
 // on a pass's rows, so every pass of a context, and of contexts that differ in K,
 // groups a row's attention sums the same way.
@@ -401,6 +409,7 @@ int attn_pages_per_workgroup(const spec_config* cfg, const spec_seq_init* seqs, 
   int longest = 0;
   for (int b = 0; b < cfg->batch; ++b) longest = std::max(longest, seqs[b].prefix_len);
   const int most = (int)(((long long)longest + half) / kAttnChunk) + 1;
+  if (!one_round(most, 0)) return std::min(most, kAttnManyPages);
   int ppw = 1;
   while (ppw < most && !(one_round(ppw, 0) && one_round(ppw, half))) ++ppw;
   return ppw;

@@ -126,6 +126,15 @@ def test_attention_page_rule_takes_one_page_up_to_one_workgroup_per_cu():
     assert _attn_pages(4, [8192], 20, 8) == 3    # two pages: 260, a few more than one per CU
 
 
+def test_attention_page_rule_where_no_count_fits_one_round():
+    # sequences x kv heads that no count brings into one round: a few more than
+    # 256, more than 512
+    assert _attn_pages(32, [2048] * 16, 20, 8) == 33   # 512: whole sequences
+    assert _attn_pages(33, [2048] * 16, 20, 8) == 10
+    assert _attn_pages(32, [2048] * 9, 20, 8) == 10    # 288
+    assert _attn_pages(33, [200] * 16, 20, 8) == 4     # prompts shorter than that
+
+
 @pytest.mark.parametrize("mutate,needle", [
     (lambda c, s: setattr(c, "K", 17), "K out of range"),
     (lambda c, s: setattr(c, "batch", 0), "batch"),

@@ -5,8 +5,11 @@ pass run on the batched-row GEMM, with caches in shuffled KV pages.
     logits, accept lengths, commits and new K/V rows against the oracle, then
     the speculative loop to the token budget, every committed token checked
     against the oracle's logits over the sequence's own history;
-  * 8 tiny scenes with K = 16 and 4 q heads per kv head (136 rows, two
-    attention row blocks);
+  * 8 tiny scenes with K = 16 and 4 q heads per kv head (136 rows; 68 query
+    rows per kv head, which one 8-wave attention workgroup takes);
+  * the multi-page attention in its 4- and 8-wave forms at both head widths,
+    with one and two row blocks, over one and several scenes;
+  * the wide-unit GEMM at hidden sizes of half a 32-column step and past 4096;
   * the same 16 scenes with K = 6 and 9 (112 and 160 rows: 7 and 10 row
     blocks of the wide-unit GEMM), and passes of 32, 33 and 48 rows (the
     boundary of the packed GEMV);
@@ -309,6 +312,59 @@ def test_attention_page_groups(K):
     T, _ = S.oracle_decoders(w, src)
     s = _session(w, provider=src, page_seed=8)
     _verify_against_oracle(w, s, T, seed=4, check_kv=(0, 15))
+
+
+# (head_dim, q heads, kv heads, K, prompts): more than 64 query rows per kv head (the 8-wave form) unless noted
+PAGE_FORMS = {
+    "64 wide": (64, 32, 8, 16, (1087, 1088, 1283)),
+    "64 wide, one scene": (64, 32, 8, 16, (2240,)),
+    "64 wide, two row blocks": (64, 32, 4, 16, (1407, 1408, 1601)),          # 136 query rows per kv head
+    "128 wide": (128, 16, 4, 16, (1407, 1408, 1601)),
+    "128 wide, two row blocks": (128, 32, 4, 16, (1407, 1408, 1601)),
+    "128 wide, 4 waves": (128, 16, 4, 4, (1407, 1408, 1601)),                # 20 query rows
+}
+
+
+@pytest.mark.parametrize("form", PAGE_FORMS)
+def test_attention_page_forms(form):
+    from paper_2606_31160_amd import binding as B
+    D, nq, nkv, K, lens = PAGE_FORMS[form]
+    base = W.get("C1")
+    t = dataclasses.replace(base.target, q_heads=nq, kv_heads=nkv, head_dim=D, mrope_section=(D // 8, D // 8, D // 4))
+    w = base.with_(target=t, draft=None, K=K, seqs=tuple(W.c5_layout(n) for n in lens), p_accept=(0.8,) * len(lens))
+    src = W.HostWeights(w)
+    T, _ = S.oracle_decoders(w, src)
+    s = _session(w, provider=src, page_seed=9)
+    assert B.spec_debug_attn_pages(s.cfg, s.seqs) >= 2
+    _verify_against_oracle(w, s, T, seed=14, check_kv=(0, len(lens) - 1))
+    s.close()
+
+
+@pytest.mark.parametrize("hidden,ffn,K", [(272, 688, 4), (272, 80, 9), (4112, 80, 4), (4128, 144, 4)])
+def test_wide_gemm_hidden_remainders(hidden, ffn, K):
+    # 80 and 160 rows on the wide-unit GEMM; 272 and 4112 are half a 32-column step past a whole one, whose
+    # activations are read row-major, 4112 and 4128 more columns than one round of the row kernels
+    base = W.get("C1")
+    w = _scenes(base.with_(target=dataclasses.replace(base.target, hidden=hidden, ffn=ffn), draft=None, K=K),
+                16, 430, 600, seed=33)
+    src = W.HostWeights(w)
+    T, _ = S.oracle_decoders(w, src)
+    s = _session(w, provider=src, page_seed=4)
+    _verify_against_oracle(w, s, T, seed=10, check_kv=(0, 15))
+    s.close()
+
+
+def test_sixteen_scenes_spec_loop_half_step_hidden():
+    # ... and the whole loop with a draft there: the first draft step's full rows, the one-row steps, idle scenes
+    base = W.get("C1")
+    w = _scenes(base.with_(target=dataclasses.replace(base.target, hidden=272),
+                           draft=dataclasses.replace(base.draft, hidden=272)), 16, 430, 600, seed=34)
+    src = W.HostWeights(w)
+    T, _ = S.oracle_decoders(w, src)
+    s = _session(w, provider=src, page_seed=4)
+    outs = _loop(s)
+    s.close()
+    _check_history(w, T, outs)
 
 
 @pytest.mark.parametrize("batch,path", [(1, "packed"), (1, "rowmajor"), (16, "packed"), (16, "rowmajor")])

@@ -15,7 +15,10 @@ at slot t takes the input e + W_in [e; f(t-1)].
     features and the draft's layer-0 context K/V against the oracle on both
     paths and at 7B width, greedy equivalence;
   * one target layer at 7B width with the 2-layer draft: features and
-    proposals against the oracle.
+    proposals against the oracle;
+  * the cross-attention form with several cache pages per attention workgroup;
+  * all three forms over 16 scenes, whose 80-row passes run on the wide-unit
+    GEMM.
 """
 import numpy as np
 import pytest
@@ -197,4 +200,72 @@ def test_conditioned_draft_7b_width():
     s = _session(w, source="device", provider=src, cond_layers=(0, 0, 0))
     seq = S.oracle_sequence(w, 0, T, D, kv=S.device_kv, cond=S.conditioning(w, src, (0, 0, 0)))
     _rounds(w, s, seq, trace, block=False, rounds=2)
+    s.close()
+
+
+def test_cross_attention_conditioned_draft_page_groups():
+    # several pages per attention workgroup in every layer, the draft's context layer among them
+    import dataclasses
+    from paper_2606_31160_amd import binding as B
+    base = W.get("C1")
+    w = base.with_(target=dataclasses.replace(base.target, q_heads=16, kv_heads=8),
+                   draft=dataclasses.replace(base.draft, q_heads=16, kv_heads=8), seqs=(W.c5_layout(2302),))
+    hp = W.HostWeights(w)
+    T, D = S.oracle_decoders(w, hp)
+    trace = OS.greedy_trace(S.oracle_sequence(w, 0, T, None, with_draft=False))
+    s = _session(w, provider=hp, cond_layers=LAYERS_TINY, cond_cross=True)
+    assert B.spec_debug_attn_pages(s.cfg, s.seqs) >= 2
+    seq = S.oracle_sequence(w, 0, T, D, cond=S.conditioning(w, hp, LAYERS_TINY, cross=True))
+    _rounds(w, s, seq, trace, block=False, rounds=3, cross=True)   # the third round's rows pass slot 2304, a page's end
+    s.close()
+
+
+@pytest.mark.parametrize("form", ["input", "cross", "block"])
+def test_conditioned_draft_sixteen_scenes(form):
+    from paper_2606_31160_amd import binding as B
+    lens = np.random.default_rng(35).integers(430, 601, size=16)
+    w = W.get("C1").with_(seqs=tuple(W.c5_layout(int(n)) for n in lens), p_accept=(0.8,) * 16)
+    assert w.batch * (w.K + 1) == 80
+    cross, block = form == "cross", form == "block"
+    hp = W.HostWeights(w)
+    T, D = S.oracle_decoders(w, hp)
+    s = _session(w, provider=hp, page_seed=6, flags=B.SPEC_FLAG_BLOCK_DRAFT if block else 0, cond_layers=LAYERS_TINY,
+                 cond_cross=cross)
+    assert B.spec_debug_path(s.ctx) == "packed"
+    sample = (0, 7, 15)
+    cond = S.conditioning(w, hp, LAYERS_TINY, cross=cross)
+    seqs = {b: S.oracle_sequence(w, b, T, D, cond=cond) for b in sample}
+    traces = {b: OS.greedy_trace(S.oracle_sequence(w, b, T, None, with_draft=False), 2 * w.K + 2) for b in sample}
+    same = dict.fromkeys(sample, True)
+    drafts = np.random.default_rng(36).integers(0, w.vocab, size=(w.batch, w.K)).astype(np.int32)
+    for _ in range(2):
+        s.draft_steps(w.K)
+        gpu = s.dtok.cpu().numpy()
+        for b, seq in seqs.items():
+            if block:
+                props, z = seq.block_propose(w.vocab - 1)
+            else:
+                z = np.stack([seq.draft_step()[1] for _ in range(w.K)])
+                props = seq.props
+            if same[b]:
+                pinned = S.check_argmax_rows(gpu[b], z)
+                same[b] = bool(pinned.all()) and list(gpu[b]) == list(props)
+            i = len(seq.generated)
+            drafts[b] = traces[b][i:i + w.K]
+        s.verify(drafts)
+        s.commit()
+        coms = s.committed()[0]
+        for b, seq in seqs.items():
+            seq.verify(drafts[b])
+            assert coms[b] == seq.committed[-len(coms[b]):]
+            P, n = w.seqs[b].prefix_len, seq.seq_len
+            got = ON.decode(s.feature(b, P, n - P))
+            for r in range(n - P):
+                assert S.normwise_err(got[r], seq.feat[P + r]) <= S.LOGIT_RTOL, (b, r)
+            if cross:
+                for which, ref in ((0, seq.dc.k[0]), (1, seq.dc.v[0])):
+                    ctx = ON.decode(s.kv(b, 1, 0, which, P, n - P))
+                    for r in range(n - P):
+                        assert S.normwise_err(ctx[r], ref[P + r]) <= S.LOGIT_RTOL, (b, which, r)
+    assert s.sync() == 0
     s.close()

@@ -17,7 +17,9 @@ on each mass and on the entropy; the three masses sum to 1 within 1e-5.
   * the draft's layer-0 cross-attention (SPEC_FLAG_COND_CROSS), the layer the
     paper's table reads, with FlatRoPE and with M-RoPE;
   * 7B-class width, one layer over the 3328-token two-frame prompt;
-  * the paper backbone width (32 heads, interleaved M-RoPE), 17 verify rows.
+  * the paper backbone width (32 heads, interleaved M-RoPE), 17 verify rows;
+  * target and draft readouts of 16 scenes, whose 80-row passes run on the
+    wide-unit GEMM.
 """
 import dataclasses
 
@@ -220,3 +222,34 @@ def test_readout_paper_backbone_width_17_rows():
     drafts = np.random.default_rng(9).integers(0, w.vocab, size=w.K).astype(np.int32)
     got, ref = _target_case(w, W.DeviceWeights(w), 0, drafts, device=True)
     _check(got, ref)
+
+
+def test_readout_sixteen_scenes():
+    lens = np.random.default_rng(37).integers(430, 601, size=16)
+    w = W.get("C1").with_(seqs=tuple(W.c5_layout(int(n)) for n in lens), p_accept=(0.8,) * 16)
+    assert w.batch * (w.K + 1) == 80
+    hp = W.HostWeights(w)
+    drafts = np.random.default_rng(10).integers(0, w.vocab, size=(w.batch, w.K)).astype(np.int32)
+    s = _session(w, provider=hp, page_seed=7)
+    dr = s.attn_readout(1, 0)
+    s.draft_step()
+    first = s.dtok.cpu().numpy()[:, 0]
+    tg = s.attn_readout(0, 1)
+    s.verify(drafts, logits=True)
+    s.commit()
+    T, D = S.oracle_decoders(w, hp, mirror=True)
+    for b in (0, 8, 15):
+        seq = S.oracle_sequence(w, b, T, D)
+        for dec, layer in ((T, 1), (D, 0)):
+            dec.readout_layer = layer
+            dec.readout_classes = OB.slot_classes(w.seqs[b].prefix_len, _blocks(w, b), seq.cap)
+        d, z = seq.draft_step()
+        _check(dr[b, :1].cpu().numpy(), D.readout)
+        assert bool(dr[b, 1:].isnan().all())
+        S.check_argmax_rows([first[b]], z[None, :])
+        ref = seq.verify(drafts[b])
+        _check(tg[b].cpu().numpy(), T.readout)
+        gl = s.logits[b].float().cpu().numpy()
+        for j in range(w.K + 1):   # the rows after the readout layer go on as in a plain pass
+            assert S.normwise_err(gl[j], ref.logits[j]) <= S.LOGIT_RTOL, (b, j)
+    s.close()

@@ -374,8 +374,8 @@ bool sg_build_one(Ctx& c, bool fill) {
 constexpr int kAttnManyPages = 10;
 
 // Pages per attention workgroup: the fewest with which the workgroups (target kv
-// heads x page groups) run in one round, both for the prompts and halfway through
-// the token budget.
+// heads x page groups) run in one round: for the prompts, and where the token
+// budget is more than twice their average, halfway through it too.
 //   One round: two workgroups per CU, but not a few more than one per CU, whose
 // second ones would take as long again (the paper backbone's 4096 tokens: 2
 // pages, 264 workgroups 14.7 us, 3 pages, 176 workgroups 11.1 us).  One page
@@ -386,7 +386,10 @@ constexpr int kAttnManyPages = 10;
 //   The budget: the count stays for the context's life, and what fits 16 scenes
 // of 200 tokens (one page, 256 workgroups) runs in nine rounds 2048 tokens later
 // (4 layers: 837 us against 779 with the three pages taken here, 751 with the
-// best count, 5).
+// best count, 5).  Where the prompts are the larger part they decide alone: a count
+// for the longer contexts as well costs the first rounds what it gives the last
+// (2048 tokens after 5 and 16 scenes of 2300 and 4900 on average: the first verify
+// 720 -> 727 and 1013 -> 1031 us).
 //   Where even one workgroup per sequence and kv head does not fit (a few more
 // than one per CU, or more than two), no count does, and whole sequences in series
 // leave the last ones alone on the chip: kAttnManyPages pages (2 layers, 16 scenes
@@ -397,7 +400,9 @@ constexpr int kAttnManyPages = 10;
 // on a pass's rows, so every pass of a context, and of contexts that differ in K,
 // groups a row's attention sums the same way.
 int attn_pages_per_workgroup(const spec_config* cfg, const spec_seq_init* seqs, int ncu) {
-  const int half = cfg->max_new_tokens / 2;
+  long long prompts = 0;
+  for (int b = 0; b < cfg->batch; ++b) prompts += seqs[b].prefix_len;
+  const int half = cfg->max_new_tokens / 2 > prompts / cfg->batch ? cfg->max_new_tokens / 2 : 0;
   auto one_round = [&](int ppw, int grown) {
     long long wgs = 0;
     for (int b = 0; b < cfg->batch; ++b) {

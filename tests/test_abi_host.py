@@ -115,6 +115,10 @@ def test_attention_page_rule_counts_the_tokens_to_come():
     assert _attn_pages(4, [200] * 16, 20, 8) == 1
     assert _attn_pages(4, [200] * 16, 2048, 8) == 3
     assert _attn_pages(4, [200] * 16, 2048, 0) == 3
+    # longer prompts than half the budget decide alone
+    scenes = [q.prefix_len for q in W.get("C5").seqs]
+    assert _attn_pages(4, scenes, 2048, 8) == _attn_pages(4, scenes, 20, 8) == 11
+    assert _attn_pages(4, [517, 1290, 2311, 3071, 4444], 2048, 8) == 2
     # the prompts' own round still counts: 8 x 65 pages, two per workgroup = 264
     assert _attn_pages(8, [4096], 20, 16) == 3
 

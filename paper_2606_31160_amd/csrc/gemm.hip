@@ -826,7 +826,12 @@ WidePlan wide_plan(int epi, int N, int Kd, int M, int ncu) {
     p.S = S;
     p.G = std::max(1, std::min(ncu / S, units));
     const int upw = (units + p.G - 1) / p.G;                 // units of the busiest workgroup
-    const int pmax = epi == EPI_ARGMAX ? 10 : 7;
+    // Few long chunks before many k-groups: each chunk stages all of x again.  10
+    // units are the workers of the wider passes (chunks of 7 at 144 rows: LM head
+    // 152064 x 3584 226 us against 205, gate/up of 32768 x 3584 99 against 82, down
+    // of 8192 x 28672 106 against 86; of 5: 241, 99 and 104).
+    constexpr int pmax = 10;
+    static_assert(pmax <= wide_workers(SPEC_MAX_ROWS / 16), "a worker per unit of a chunk");
     const int chunks = (upw + pmax - 1) / pmax;
     p.P = (upw + chunks - 1) / chunks;
     // as many k-groups as the workers and the LDS (two stage buffers, half of

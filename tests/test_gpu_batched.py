@@ -354,6 +354,33 @@ def test_wide_gemm_hidden_remainders(hidden, ffn, K):
     s.close()
 
 
+@pytest.mark.parametrize("K", [4, 8])
+@pytest.mark.parametrize("ffn", [28688, 40960, 40976])
+def test_wide_gemm_units_per_chunk(ffn, K):
+    # gate/up of 8, 10 and 11 units per workgroup (256 CUs): a chunk of 8, of 10, two of 6; 80 and 144 rows
+    base = W.get("C1")
+    w = _scenes(base.with_(target=dataclasses.replace(base.target, layers=1, hidden=64, ffn=ffn), draft=None, K=K),
+                16, 430, 600, seed=36)
+    src = W.HostWeights(w)
+    T, _ = S.oracle_decoders(w, src)
+    s = _session(w, provider=src, page_seed=4)
+    _verify_against_oracle(w, s, T, seed=11, check_kv=(0, 15))
+    s.close()
+
+
+def test_wide_gemm_partial_sums_of_eight_units():
+    # a down projection of 256 units in 8 k-splits: 8 units per workgroup, one k-group, whose partial sums go
+    # straight from the accumulators to memory
+    base = W.get("C1")
+    w = _scenes(base.with_(target=dataclasses.replace(base.target, layers=1, hidden=8192, ffn=12288), draft=None, K=10),
+                3, 430, 460, seed=38)
+    src = W.DeviceWeights(w)
+    T, _ = S.oracle_decoders(w, src, cache_weights=True)
+    s = _session(w, source="device", provider=src, page_seed=4)
+    _verify_against_oracle(w, s, T, seed=12, kv=S.device_kv)
+    s.close()
+
+
 def test_sixteen_scenes_spec_loop_half_step_hidden():
     # ... and the whole loop with a draft there: the first draft step's full rows, the one-row steps, idle scenes
     base = W.get("C1")

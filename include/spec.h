@@ -78,7 +78,7 @@ typedef struct spec_dims {
 #define SPEC_FLAG_NO_GRAPHS 1      /* launch kernels one by one instead of replaying HIP graphs */
 /* (values 2 and 4 are not used; unknown flag bits are rejected with SPEC_E_INVAL) */
 #define SPEC_FLAG_ROWMAJOR 8       /* stream the caller's row-major weights directly.  Without it, passes
-                                      on the layered path of at most 16 rows (batch*(K+1) <= 16), or of
+                                      of at most 32 rows (batch*(K+1) <= 32), or of
                                       rows the batched-row GEMM takes, stream a tile-packed copy of every
                                       weight matrix that spec_init writes into the workspace (its size is
                                       part of spec_workspace_bytes) */

@@ -5,7 +5,9 @@
 //   * k_gemm_wide (below k_gemm): passes of more than 32 rows over the
 //     tile-packed weights (several sequences verified together);
 //   * k_gemm: row-major weights (SPEC_FLAG_ROWMAJOR) for passes of more than
-//     16 rows, and 17..32-row passes whose width the thin GEMV cannot stage.
+//     16 rows, 17..32-row passes whose width the thin GEMV cannot stage, and
+//     the q/k/v projection of wider packed passes where it is not k-split
+//     (narrow models).
 //
 // k_gemm: a workgroup owns kGemmTiles = 4 output tiles of 16 columns and the k-range
 // of split blockIdx.y, walked in chunks of 32 * kSteps columns (kSteps
@@ -416,18 +418,19 @@ __global__ __launch_bounds__(threads_for(MB)) void k_gemm(GemvArgs a) {
 //
 // A unit is a pair of tiles (32 output columns; a gate/up pair).  A workgroup
 // takes a contiguous run of units over the k-range of its split, walked in
-// chunks of at most P units.  Wave 0 only stages x; P x KG worker waves
+// chunks of at most P units.  Two loader waves only stage x; P x KG worker waves
 // multiply: worker (p, kg) owns unit p of the chunk and, of every stage of
 // KG x NS k-steps, the kg-th NS steps, for all row blocks, so that each x
 // operand read from LDS feeds two MFMAs and each weight block MB of them.
 //
-// x: the loader wave stages a stage's x operands (all rows) by buffer-to-LDS
-// loads, in MFMA operand order (block rb of a step: 16 rows x 32 columns, lane
-// l's 16 bytes at 16 l), into one of two LDS buffers while the workers use the
-// other; one workgroup barrier per stage.  Weights go straight to the workers'
-// registers, kWideDepth steps ahead.  With x in a wave of its own, a worker's
-// only outstanding memory operations are its weight loads, so the compiler's
-// wait counts are exact and the loads stay in flight across the barriers.
+// x: the loaders stage each stage's x operands (all rows, a share each) by
+// buffer-to-LDS loads, in MFMA operand order (block rb of a step: 16 rows x 32
+// columns, lane l's 16 bytes at 16 l), into a ring of 2 to kWideStages LDS
+// buffers, as many as fit, all but one ahead of the workers; one workgroup
+// barrier per stage.  Weights go straight to the workers' registers, kWideDepth
+// steps ahead.  With x in waves of its own, a worker's only outstanding memory
+// operations are its weight loads, so the compiler's wait counts are exact and
+// the loads stay in flight across the barriers.
 //
 // What bounds it: the weights, read once from HBM, then the work at both ends
 // of a launch.  x comes from the XCD's L2 (a workgroup reads up to 112 GB/s per
@@ -436,9 +439,9 @@ __global__ __launch_bounds__(threads_for(MB)) void k_gemm(GemvArgs a) {
 // re-reading x is cheaper than writing and re-reading fp32 partial sums.  One
 // barrier per stage instead of per k-step, x in waves of its own, and no 64-bit
 // division, dependent load or unrolled epilogue around the loop: at 144 rows
-// and 7B widths gate/up 87 -> 56 us, LM head 315 -> 207, down 40 -> 33, q/k/v
-// 21 -> 17, o 22 -> 14.5; at 45 rows 51 -> 45, 201 -> 182, 27 (unchanged), 15 ->
-// 11.6 and 15 -> 9.4.  Of the 56 us, 42 are the loop (39 us of weights at the
+// and 7B widths gate/up 87 -> 56 us, LM head 315 -> 205, down 40 -> 33, q/k/v
+// 21 -> 16, o 22 -> 15; at 45 rows 51 -> 45, 201 -> 182, 27 (unchanged), 15 ->
+// 10 and 15 -> 9.  Of the 56 us, 42 are the loop (39 us of weights at the
 // read rate), 4 the time to the first staged x and 5 the epilogue.
 //
 // A weight load past the k-range or the unit range gets an offset past the
@@ -834,8 +837,8 @@ WidePlan wide_plan(int epi, int N, int Kd, int M, int ncu) {
     static_assert(pmax <= wide_workers(SPEC_MAX_ROWS / 16), "a worker per unit of a chunk");
     const int chunks = (upw + pmax - 1) / pmax;
     p.P = (upw + chunks - 1) / chunks;
-    // as many k-groups as the workers and the LDS (two stage buffers, half of
-    // the groups' partial tiles) allow
+    // as many k-groups as the workers and the LDS (two stage buffers) allow; the
+    // groups' partial tiles pass through it as many row blocks at a time as fit
     p.KG = std::max(1, std::min(wide_workers(mb) / p.P, (T + S - 1) / S));
     while (p.KG > 1 && (size_t)2 * p.KG * mb * 1024 > kWideRing)
       --p.KG;

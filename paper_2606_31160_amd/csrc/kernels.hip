@@ -1139,8 +1139,11 @@ __global__ __launch_bounds__(NW * 64, (NW == 8 && !RO) ? 6 : 1) void k_attn(Attn
 //
 // What bounds it: reading the pages from HBM once, so the loads must never
 // stop.  A wave of its own copies pages into two LDS buffers by buffer-to-LDS
-// loads, one page ahead of the NW waves that multiply; 64 KB per workgroup, two
-// workgroups and 128 KB in flight per CU, no registers held by loads.  The rows
+// loads, one page ahead of the NW waves that multiply; 64 KB per workgroup at D =
+// 128, no registers held by loads.  The 4-wave form runs two workgroups per CU;
+// the 8-wave form's 105 registers leave room for one, and a second waits.  (Built
+// at 88 registers, two per CU, it was no faster: 352 workgroups of two 4096-token
+// paper scenes, 4 layers 536 us against 532; 440 of five 664 against 655.)  The rows
 // in LDS have no padding (the loads write runs of 1 KB); instead the 16-byte
 // chunks of a row are permuted by an xor with row bits so that the eight lanes
 // that an LDS read serves together fall in distinct banks:
@@ -1816,8 +1819,8 @@ hipError_t launch_attention(Ctx& c, Model& m, int li) {
   const int G = nq / nkv;
   const bool ro = c.ro_out && c.ro_m == &m && c.ro_layer == li;
   const int cross = (c.cross && &m == &c.drf && li == 0) ? 1 : 0;
-  // several pages per workgroup where the context asks for it (many
-  // sequences); a readout pass keeps one page per workgroup
+  // the context's pages per workgroup (attn_pages_per_workgroup); a readout pass
+  // keeps one
   const int ppw = ro ? 1 : c.attn_ppw;
   // query rows of one kv head (rows per sequence x q heads per kv head): up
   // to 64 in one workgroup of 4 waves; more (e.g. 17 rows x 4 heads) in

@@ -396,6 +396,11 @@ constexpr int kAttnManyPages = 10;
 // of 1 to 4 thousand tokens, 40 kv heads: 531 us whole, 478 with 10 pages; of 2048
 // tokens 485 and 430; 9 scenes, 32 kv heads: 417 and 331, 299 and 274; 8 and 12
 // pages within 3% of 10).
+//   The 8-wave form (more than 64 query rows per kv head) runs one workgroup per
+// CU and would take more pages: two 4096-token paper scenes at K = 16, 4 layers,
+// 532 us with the 3 pages (352 workgroups) taken here, 512 with 5 (208); at K = 8,
+// 4 waves, 461 and 462; 16 scenes at K = 8 in 22 pages (252 workgroups) 847 us
+// against 826 in 11.  One count has to serve every K.
 //   It depends on the prompts, the budget, the batch and the kv heads only, never
 // on a pass's rows, so every pass of a context, and of contexts that differ in K,
 // groups a row's attention sums the same way.
@@ -477,7 +482,7 @@ size_t carve(Ctx& c, const spec_config* cfg, const spec_seq_init* seqs, bool has
   c.x = cv.take<float>((size_t)L.Mpad * H);
   c.q = cv.take<bf16_t>((size_t)L.Mpad * nqD);
   c.o = cv.take<bf16_t>((size_t)L.Mpad * nqD);
-  c.u = cv.take<bf16_t>((size_t)L.Mpad * align_up(F, 32));   // row-major, or step-major for the packed path
+  c.u = cv.take<bf16_t>((size_t)L.Mpad * align_up(F, 32));   // row-major, step-major (packed GEMV) or operand order (wide-unit GEMM)
   c.xg = cv.take<bf16_t>((size_t)L.Mpad * H);
   c.xgp = (c.gemm_wide && H % 32 == 0) ? cv.take<bf16_t>((size_t)L.Mpad * H) : nullptr;
   c.ss = cv.take<float>((size_t)(H / kTile) * L.Mpad);

@@ -211,10 +211,11 @@ hipError_t launch_hold(Ctx& c, double ms);   // bounded device-side wait (timing
 hipError_t launch_rope_table(Ctx& c);        // fills cs
 hipError_t launch_prefix_kv(Ctx& c, Model& m, int layer, int b, int prefix_len,
                             const bf16_t* k_pre, const bf16_t* v);
-hipError_t launch_stage_verify(Ctx& c, const int32_t* d_override, void* d_logits);
+bf16_t* logits_target(const Ctx& c, void* d_logits);   // null if d_logits is
+hipError_t launch_stage_verify(Ctx& c, const int32_t* d_override, bf16_t* logits);
 hipError_t launch_forward(Ctx& c, PassMode mode);   // embed .. accept / draft pick
 hipError_t launch_commit(Ctx& c, int32_t* acc, int32_t* committed, int32_t* ncommit, int32_t* fin);
-hipError_t launch_logits_out(Ctx& c, void* d_logits);
+hipError_t launch_logits_out(Ctx& c, void* d_logits);   // from the staging buffer
 // Packed-weight path: plans (and, with fill, points) every GEMV job of a model;
 // false if a shape does not fit.  Packs a model's weights / the LM head.
 bool sg_build_jobs(Ctx& c, Model& m, bool draft, bool fill);

@@ -2358,17 +2358,28 @@ hipError_t launch_rope_table(Ctx& c) {
   return hipGetLastError();
 }
 
-namespace {
-// Whether the LM head can write its logits straight to the caller's array (it
-// stores four at a time).  That leaves out a copy of the logits and the gap
-// before it, 13 us after a 9-row pass and 22 after one of 144 rows.
-bool logits_direct(const void* d_logits) { return (reinterpret_cast<uintptr_t>(d_logits) & 7u) == 0; }
-}  // namespace
+// Where the LM head writes a verify's logits: the caller's array itself where a
+// kernel on this GPU can store four at a time there (8-byte alignment, memory of
+// the context's device), else the staging buffer, from which launch_logits_out
+// copies: the array may lie on another GPU or in host memory, which a copy reaches
+// and a store may not.  Writing directly leaves out the copy and the gap before
+// it, 13 us after a 9-row pass and 22 after one of 144 rows.
+bf16_t* logits_target(const Ctx& c, void* d_logits) {
+  if (!d_logits) return nullptr;
+  hipPointerAttribute_t at{};
+  if ((reinterpret_cast<uintptr_t>(d_logits) & 7u) == 0) {
+    if (hipPointerGetAttributes(&at, d_logits) != hipSuccess)
+      (void)hipGetLastError();
+    else if (at.type == hipMemoryTypeDevice && at.device == c.device)
+      return static_cast<bf16_t*>(d_logits);
+  }
+  return c.logits;
+}
 
-hipError_t launch_stage_verify(Ctx& c, const int32_t* d_override, void* d_logits) {
+hipError_t launch_stage_verify(Ctx& c, const int32_t* d_override, bf16_t* logits) {
   Timed t(c, SPEC_KERNEL_OTHER, 0);
   hipExtLaunchKernelGGL(k_stage_verify, dim3(c.B), dim3(64), 0, c.stream, t.e0, t.e1, 0, c.st, d_override, c.K, c.V,
-                        d_logits ? 1 : 0, d_logits && logits_direct(d_logits) ? static_cast<bf16_t*>(d_logits) : c.logits);
+                        logits ? 1 : 0, logits);
   return hipGetLastError();
 }
 
@@ -2564,7 +2575,6 @@ hipError_t launch_commit(Ctx& c, int32_t* acc, int32_t* committed, int32_t* ncom
 }
 
 hipError_t launch_logits_out(Ctx& c, void* d_logits) {
-  if (!d_logits || logits_direct(d_logits)) return hipSuccess;
   return hipMemcpyAsync(d_logits, c.logits, (size_t)c.M * c.V * sizeof(bf16_t), hipMemcpyDeviceToDevice, c.stream);
 }
 

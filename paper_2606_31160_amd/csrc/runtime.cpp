@@ -1106,10 +1106,11 @@ spec_status spec_verify(spec_ctx* ctx, const int32_t* d_draft_tokens, void* d_lo
     if (c.phase == Ctx::VERIFIED) return set_err(c, SPEC_E_STATE, "spec_verify: commit the last verify first");
     if (!d_draft_tokens && c.K > 0 && c.dsteps != c.K)
       return set_err(c, SPEC_E_STATE, "spec_verify: no draft tokens given and fewer than K draft steps taken");
-    HIPCHK(c, launch_stage_verify(c, c.K > 0 ? d_draft_tokens : nullptr, d_logits), "verify staging");
+    bf16_t* const logits = logits_target(c, d_logits);
+    HIPCHK(c, launch_stage_verify(c, c.K > 0 ? d_draft_tokens : nullptr, logits), "verify staging");
     spec_status s = run_pass(c, PASS_VERIFY);
     if (s != SPEC_OK) return s;
-    HIPCHK(c, launch_logits_out(c, d_logits), "logits copy");
+    if (logits != d_logits) HIPCHK(c, launch_logits_out(c, d_logits), "logits copy");
     c.phase = Ctx::VERIFIED;
     return SPEC_OK;
   });
@@ -1137,7 +1138,8 @@ spec_status spec_verify_scratch(spec_ctx* ctx, const int32_t* d_draft_tokens, vo
     // arrival counters start at zero (every launch leaves them at zero, but
     // the array is shared with every other context on this GPU)
     if (plan.cnt_bytes) HIPCHK(c, launch_zero(c, c.sg_cnt, plan.cnt_bytes), "scratch counter clear");
-    HIPCHK(c, launch_stage_verify(c, c.K > 0 ? d_draft_tokens : nullptr, d_logits), "verify staging");
+    bf16_t* const logits = logits_target(c, d_logits);
+    HIPCHK(c, launch_stage_verify(c, c.K > 0 ? d_draft_tokens : nullptr, logits), "verify staging");
     if (c.ro_arm_out && c.ro_arm_model == 0) {
       c.ro_m = &c.tgt;
       c.ro_layer = c.ro_arm_layer;
@@ -1150,7 +1152,7 @@ spec_status spec_verify_scratch(spec_ctx* ctx, const int32_t* d_draft_tokens, vo
     c.ro_m = nullptr;
     c.ro_out = nullptr;
     HIPCHK(c, e, "forward pass");
-    HIPCHK(c, launch_logits_out(c, d_logits), "logits copy");
+    if (logits != d_logits) HIPCHK(c, launch_logits_out(c, d_logits), "logits copy");
     c.phase = Ctx::VERIFIED;
     return SPEC_OK;
   });

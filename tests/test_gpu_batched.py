@@ -414,3 +414,24 @@ def test_logits_at_any_address(tiny16, batch, path):
         assert (buf[:off] == 7).all() and (buf[off + n:] == 7).all()
         s.close()
     assert all(torch.equal(got[0], g) for g in got[1:])
+
+
+@pytest.mark.parametrize("batch,scratch", [(1, False), (1, True), (16, False)])
+def test_logits_to_host_memory(tiny16, batch, scratch):
+    # an array that is not this GPU's own memory takes the copy, as one on another GPU does: same bits
+    import torch
+    from paper_2606_31160_amd import binding as B
+    w, hp, T = tiny16
+    w = w.with_(seqs=w.seqs[:batch], p_accept=w.p_accept[:batch])
+    drafts = torch.arange(batch * w.K, dtype=torch.int32, device="cuda").reshape(batch, w.K) % w.vocab
+    n = batch * (w.K + 1) * w.vocab
+    got = []
+    for pinned in (False, True):
+        s = _session(w, provider=hp, page_seed=3 if batch > 1 else None)
+        buf = (torch.full((n,), 7.0, dtype=torch.bfloat16, pin_memory=True) if pinned
+               else torch.full((n,), 7.0, dtype=torch.bfloat16, device="cuda"))
+        (B.spec_verify_scratch if scratch else B.spec_verify)(s.ctx, drafts.data_ptr(), buf.data_ptr())
+        torch.cuda.synchronize()
+        got.append(buf.cpu().clone())
+        s.close()
+    assert torch.equal(got[0], got[1])

@@ -374,22 +374,32 @@ bool sg_build_one(Ctx& c, bool fill) {
 constexpr int kAttnManyPages = 10;
 
 // Pages per attention workgroup: the fewest with which the workgroups (target kv
-// heads x page groups) run in one round: for the prompts, and where the token
-// budget is more than twice their average, halfway through it too.
+// heads x page groups) of the prompts run in one round, and where the token budget
+// is more than twice their average, those a quarter of the budget later do too.
 //   One round: two workgroups per CU, but not a few more than one per CU, whose
 // second ones would take as long again (the paper backbone's 4096 tokens: 2
 // pages, 264 workgroups 14.7 us, 3 pages, 176 workgroups 11.1 us).  One page
 // (k_attn) only where that is at most one workgroup per CU: past it two pages in
 // k_attn_pages are faster (7B, 4 layers, one scene of 4096, 5120, 6144 and 8192
 // tokens, 260 to 516 one-page workgroups: 442, 446, 448 and 455 us with one page,
-// 429, 432, 440 and 445 with two).
+// 429, 432, 440 and 445 with two; ragged scenes with one of 4875 or more 574 and 554,
+// 586 and 566; little where none is over 2048: 412 and 412, 495 and 496, 540 and 545).
 //   The budget: the count stays for the context's life, and what fits 16 scenes
-// of 200 tokens (one page, 256 workgroups) runs in nine rounds 2048 tokens later
-// (4 layers: 837 us against 779 with the three pages taken here, 751 with the
-// best count, 5).  Where the prompts are the larger part they decide alone: a count
-// for the longer contexts as well costs the first rounds what it gives the last
-// (2048 tokens after 5 and 16 scenes of 2300 and 4900 on average: the first verify
-// 720 -> 727 and 1013 -> 1031 us).
+// of 200 tokens (one page, 256 workgroups) runs in nine rounds 2048 tokens later.  A
+// quarter is the middle of a generation that uses half of its budget; counts for
+// later cost the first rounds more.  4 layers, at 0, a quarter, half and all of the
+// budget: those 16 scenes 690, 711, 738 and 801 us with one page, 692, 708, 737 and 774
+// with the two taken here, 697, 709, 723 and 770 with three; 9 scenes of 1200 tokens,
+// 6144 to come, 620, 671, 702 and 777 with the two of the prompts, 625, 654, 691 and 746
+// with the four taken here, 630, 659, 670 and 751 with five; 9 paper scenes of 300
+// tokens 730, 825, 924 and 1119 with two, 726, 787, 888 and 1003 with the five taken
+// here, 749, 819, 843 and 998 with nine; 16 tiny ones 240, 247, 263 and 284 with two,
+// 243, 247, 254 and 280 with the three taken here, 248, 255, 260 and 271 with five.
+//   Where two per CU hold the later workgroups, more pages only cost (3 scenes of 400
+// tokens, 2048 to come: one page 531, 564, 570 and 573 us, two 535, 561, 568 and 573; 2
+// short paper scenes 389, 401, 406 and 412, two 403, 400, 404 and 413).  Longer prompts
+// decide alone (2048 tokens after 5 and 16 scenes of 2300 and 4900: a count for the
+// longer contexts as well took the first verify from 720 to 727 and from 1013 to 1031).
 //   Where even one workgroup per sequence and kv head does not fit (a few more
 // than one per CU, or more than two), no count does, and whole sequences in series
 // leave the last ones alone on the chip: kAttnManyPages pages (2 layers, 16 scenes
@@ -407,21 +417,25 @@ constexpr int kAttnManyPages = 10;
 int attn_pages_per_workgroup(const spec_config* cfg, const spec_seq_init* seqs, int ncu) {
   long long prompts = 0;
   for (int b = 0; b < cfg->batch; ++b) prompts += seqs[b].prefix_len;
-  const int half = cfg->max_new_tokens / 2 > prompts / cfg->batch ? cfg->max_new_tokens / 2 : 0;
-  auto one_round = [&](int ppw, int grown) {
+  const int later = cfg->max_new_tokens / 2 > prompts / cfg->batch ? cfg->max_new_tokens / 4 : 0;
+  auto workgroups = [&](int ppw, int grown) {
     long long wgs = 0;
     for (int b = 0; b < cfg->batch; ++b) {
       const long long pages = ((long long)seqs[b].prefix_len + grown) / kAttnChunk + 1;
       wgs += cfg->target.kv_heads * ((pages + ppw - 1) / ppw);
     }
+    return wgs;
+  };
+  auto one_round = [&](int ppw) {
+    const long long wgs = workgroups(ppw, 0);
     return wgs <= ncu || (ppw > 1 && wgs > ncu + ncu / 8 && wgs <= 2ll * ncu);
   };
   int longest = 0;
   for (int b = 0; b < cfg->batch; ++b) longest = std::max(longest, seqs[b].prefix_len);
-  const int most = (int)(((long long)longest + half) / kAttnChunk) + 1;
-  if (!one_round(most, 0)) return std::min(most, kAttnManyPages);
+  const int most = (int)(((long long)longest + later) / kAttnChunk) + 1;
+  if (!one_round(most)) return std::min(most, kAttnManyPages);
   int ppw = 1;
-  while (ppw < most && !(one_round(ppw, 0) && one_round(ppw, half))) ++ppw;
+  while (ppw < most && !(one_round(ppw) && workgroups(ppw, later) <= 2ll * ncu)) ++ppw;
   return ppw;
 }
 

@@ -113,8 +113,15 @@ def test_attention_page_rule_counts_the_tokens_to_come():
     # take more pages than the prompts alone would (16 x 4 pages x 4 kv heads =
     # 256 workgroups), and the count does not depend on K
     assert _attn_pages(4, [200] * 16, 20, 8) == 1
-    assert _attn_pages(4, [200] * 16, 2048, 8) == 3
-    assert _attn_pages(4, [200] * 16, 2048, 0) == 3
+    assert _attn_pages(4, [200] * 16, 2048, 8) == 2
+    assert _attn_pages(4, [200] * 16, 2048, 0) == 2
+    # 11 and 12 sequences of 300 + 576 tokens: 616 and 672 workgroups of one page, 308 and 336 of two
+    assert _attn_pages(4, [300] * 11, 2304, 8) == 2
+    assert _attn_pages(4, [300] * 12, 2304, 8) == 2
+    # what two workgroups per CU hold later takes the prompts' count
+    assert _attn_pages(4, [300] * 9, 2304, 8) == 1    # 504
+    assert _attn_pages(4, [349, 248, 619], 2048, 8) == 1
+    assert _attn_pages(8, [148, 131], 2048, 4) == 1
     # longer prompts than half the budget decide alone
     scenes = [q.prefix_len for q in W.get("C5").seqs]
     assert _attn_pages(4, scenes, 2048, 8) == _attn_pages(4, scenes, 20, 8) == 11

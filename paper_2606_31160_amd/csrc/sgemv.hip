@@ -150,9 +150,8 @@ __device__ __forceinline__ void epilogue(const SgJob& j, RowInfo& ri, int rb, in
     }
   } else {   // SG_ARGMAX
     const f32x4 y = ya * ri.inv_rms;
-    const int N = j.ntiles * 16, n = 16 * u + 4 * grp;
-    if (ri.logits)
-      st_global(ri.logits + n, u32x2{pack2(y.x, y.y), pack2(y.z, y.w)});
+    const int n = 16 * u + 4 * grp;
+    if (ri.logits) st_global(ri.logits + n, u32x2{pack2(y.x, y.y), pack2(y.z, y.w)});
     float best = -INFINITY;
     int bi = n;
     int nan = 0;

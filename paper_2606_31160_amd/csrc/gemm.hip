@@ -506,7 +506,7 @@ __global__ __launch_bounds__((wide_workers(MB) + kWideLoaders) * 64) void k_gemm
   __shared__ float inv_rms[ROWS];       // 0 for rows past the pass or idle
   __shared__ int live_s[ROWS];
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
-  const int M = a.M, N = a.N, T = (a.Kd + 31) >> 5, ntiles = N / kTile, nunits = (ntiles + 1) >> 1;
+  const int M = a.M, N = a.N, T = (a.Kd + 31) >> 5, ntiles = N / kTile;
   // The divisions are the host's: the code ahead of the first loads is fetched
   // cold by every launch.
   const int P = a.wp, KG = a.wkg, NB = a.wnb, nch = a.wnch, cu = a.wcu, nst = a.wnst;

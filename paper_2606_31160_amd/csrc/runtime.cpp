@@ -375,7 +375,8 @@ constexpr int kAttnManyPages = 10;
 
 // Pages per attention workgroup: the fewest with which the workgroups (target kv
 // heads x page groups) of the prompts run in one round, and where the token budget
-// is more than twice their average, those a quarter of the budget later do too.
+// is more than twice their average, those a quarter of the budget later do too (up
+// to kAttnManyPages: a budget may be as good as none).
 //   One round: two workgroups per CU, but not a few more than one per CU, whose
 // second ones would take as long again (the paper backbone's 4096 tokens: 2
 // pages, 264 workgroups 14.7 us, 3 pages, 176 workgroups 11.1 us).  One page
@@ -435,7 +436,10 @@ int attn_pages_per_workgroup(const spec_config* cfg, const spec_seq_init* seqs, 
   const int most = (int)(((long long)longest + later) / kAttnChunk) + 1;
   if (!one_round(most)) return std::min(most, kAttnManyPages);
   int ppw = 1;
-  while (ppw < most && !(one_round(ppw) && workgroups(ppw, later) <= 2ll * ncu)) ++ppw;
+  while (ppw < most && !one_round(ppw)) ++ppw;
+  const int bound = std::min(most, kAttnManyPages);
+  for (int q = ppw + 1; q <= bound && workgroups(ppw, later) > 2ll * ncu; ++q)
+    if (one_round(q)) ppw = q;
   return ppw;
 }
 

@@ -122,6 +122,9 @@ def test_attention_page_rule_counts_the_tokens_to_come():
     assert _attn_pages(4, [300] * 9, 2304, 8) == 1    # 504
     assert _attn_pages(4, [349, 248, 619], 2048, 8) == 1
     assert _attn_pages(8, [148, 131], 2048, 4) == 1
+    # a budget that stands for none takes at most ten
+    assert _attn_pages(4, [200] * 16, 100000, 8) == 10
+    assert _attn_pages(4, [200], 100000, 8) == 4      # 395 pages: in fours 396 workgroups
     # longer prompts than half the budget decide alone
     scenes = [q.prefix_len for q in W.get("C5").seqs]
     assert _attn_pages(4, scenes, 2048, 8) == _attn_pages(4, scenes, 20, 8) == 11

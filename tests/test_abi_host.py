@@ -96,6 +96,13 @@ def test_benchmark_and_paper_configs_validate_on_host(name):
     assert n > 0 and n % 256 == 0
 
 
+def test_scene_layouts_fit_their_prompts():
+    # 226..255 and 377..383 tokens: 85% rounds to one grid row per camera more than fits
+    for n in range(128, 1200):
+        assert all(b.start + b.ntok <= n for b in W.c5_layout(n).blocks), n
+    assert [W.c5_layout(n).blocks[0].h for n in (128, 225, 240, 256, 376, 380, 384, 4096)] == [1, 1, 1, 2, 2, 2, 3, 27]
+
+
 def _attn_pages(kv_heads, prompts, budget, K):
     w = W.get("C1")
     cfg = _cfg(w, K=K, batch=len(prompts))

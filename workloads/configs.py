@@ -130,8 +130,9 @@ def _c3() -> Workload:
 
 def c5_layout(prefix_len: int) -> SeqLayout:
     """Four cameras, each a (2, h_c, 16) grid, placed back to back from index 0;
-    h_c is chosen so that vision fills about 85% of the prompt."""
-    h_c = max(1, int(round(0.85 * prefix_len / 128)))
+    h_c is chosen so that vision fills about 85% of the prompt, and fits it from
+    128 tokens on."""
+    h_c = max(1, min(int(round(0.85 * prefix_len / 128)), prefix_len // 128))
     blocks = tuple(VisionBlock(32 * h_c * cam, 2, h_c, 16) for cam in range(4))
     return SeqLayout(prefix_len, blocks)
 

@@ -435,3 +435,38 @@ def test_logits_to_host_memory(tiny16, batch, scratch):
         got.append(buf.cpu().clone())
         s.close()
     assert torch.equal(got[0], got[1])
+
+
+@pytest.mark.parametrize("batch", [1, 16])
+def test_logits_arrays_alternate(tiny16, batch):
+    # one context, another array in every verify (replayed graphs): aligned, none, off by two bytes, host memory,
+    # aligned again
+    import torch
+    from paper_2606_31160_amd import binding as B
+    w, hp, T = tiny16
+    w = w.with_(seqs=w.seqs[:batch], p_accept=w.p_accept[:batch])
+    n = batch * (w.K + 1) * w.vocab
+    gen = torch.Generator().manual_seed(41)
+    rounds = [torch.randint(0, w.vocab, (batch, w.K), generator=gen, dtype=torch.int32).cuda() for _ in range(5)]
+    ref, s = (_session(w, provider=hp, page_seed=3 if batch > 1 else None) for _ in range(2))
+    own = torch.empty(n, dtype=torch.bfloat16, device="cuda")
+    arrays = [torch.full((n + 4,), 7.0, dtype=torch.bfloat16, device="cuda"), None,
+              torch.full((n + 4,), 7.0, dtype=torch.bfloat16, device="cuda"),
+              torch.full((n + 4,), 7.0, dtype=torch.bfloat16, pin_memory=True),
+              torch.full((n + 4,), 7.0, dtype=torch.bfloat16, device="cuda")]
+    want = []
+    for i, (buf, d) in enumerate(zip(arrays, rounds)):
+        off = 1 if i == 2 else 0
+        B.spec_verify(ref.ctx, d.data_ptr(), own.data_ptr())
+        B.spec_verify(s.ctx, d.data_ptr(), 0 if buf is None else buf.data_ptr() + 2 * off)
+        ref.commit()
+        s.commit()
+        torch.cuda.synchronize()
+        assert ref.committed()[0] == s.committed()[0]
+        want.append((off, own.clone()))
+    for buf, (off, z) in zip(arrays, want):   # and no later verify wrote to an earlier array
+        if buf is not None:
+            b = buf.cuda()
+            assert torch.equal(b[off:off + n], z) and (b[:off] == 7).all() and (b[off + n:] == 7).all()
+    ref.close()
+    s.close()

@@ -304,6 +304,7 @@ def test_wide_gemm_unit_and_step_remainders(batch, K, vocab, ffn):
 
 @pytest.mark.parametrize("K", [1, 4])
 def test_attention_page_groups(K):
+    from paper_2606_31160_amd import binding as B
     # several cache pages per attention workgroup at head_dim 64: prompts that end just before, at and after a page and
     # a page group, groups shorter than the rest, 2 and 5 rows per sequence
     lens = [1087, 1088, 1089, 1151, 1152, 1280, 1283, 1471, 1472, 1530, 1599, 1600, 2047, 2048, 2049, 4100]
@@ -311,6 +312,7 @@ def test_attention_page_groups(K):
     src = W.HostWeights(w)
     T, _ = S.oracle_decoders(w, src)
     s = _session(w, provider=src, page_seed=8)
+    assert B.spec_debug_attn_pages(s.cfg, s.seqs) >= 2
     _verify_against_oracle(w, s, T, seed=4, check_kv=(0, 15))
 
 
